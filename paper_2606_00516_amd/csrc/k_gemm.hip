@@ -693,14 +693,41 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__
 
 // ===========================================================================
 // big: 256 x 256 output tiles for large M (prefill-sized batches).  K tiles
-// of 64 stream into a double-buffered LDS ring straight from global memory
-// (buffer loads with an LDS destination: no register round trip).  8 waves
-// (2 along M x 4 along N) each own a 128 x 64 sub-tile held in accumulation
-// registers.  The product is formed transposed, C^T = W A^T, so that each
-// lane's accumulators hold 4 consecutive output columns of one row and the
-// epilogue stores 8 bytes at a time.  LDS rows are 128 bytes (64 bf16 of
-// K); the 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7), which
-// makes the MFMA operand reads of 16 consecutive rows conflict free.
+// of 64 stream straight from global memory (buffer loads with an LDS
+// destination: no register round trip) into two LDS buffers, each cut into
+// four half tiles (rows 0..63 and 64..127 of every wave's 128 A rows, columns
+// 0..31 and 32..63 of its 64 W columns).  8 waves (2 along M x 4 along N) each
+// own a 128 x 64 sub-tile.
+//
+// What bounds it is latency on the way to the matrix cores, so two things
+// are kept apart from them.  (1) A K tile is four phases of 16 products, one
+// per quadrant (half of A x half of W); each phase reads from LDS the one
+// half tile that the next products need (W0, W1, A1, then A0 of the next K
+// tile) and issues the load of one half tile into the place that was read
+// two phases before, so six half tiles' worth of phases lie between a load
+// and its use, and the wait in each phase leaves the five youngest half tiles
+// (80 KiB per CU) in flight: the load stream never drains.  (2) The two
+// wave rows, one wave of each on every SIMD, run half a phase apart
+// (the second passes one extra barrier first): while one multiplies, the
+// other reads LDS and issues loads (raising the multiplying wave's priority
+// adds nothing).  Against one barrier and a full drain
+// per K tile: gate/up at 8192 rows (N 28672, K 4096) 1456 -> 1365 us, down
+// (N 4096, K 14336) 800 -> 691, qkv at 2048 rows 106 -> 92, 70B gate/up at
+// 256 rows 253 -> 221; without the half-phase offset 1614 / 804 us.
+//
+// Safety of the reuse: a half tile read in phase p is complete in every
+// wave (lgkmcnt(0) before its products) before the barrier that ends phase
+// p of the later wave row, and refilled in phase p + 2; a half tile read in
+// phase p was waited for by every wave before the barrier in its phase p - 1.
+//
+// The product is formed transposed, C^T = W A^T, so that each lane's
+// accumulators hold 4 consecutive output columns of one row and the epilogue
+// stores 8 bytes at a time.  LDS rows are 128 bytes (64 bf16 of K); the
+// 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7), which makes the
+// MFMA operand reads of 16 consecutive rows conflict free.  8-bit W tiles
+// stay codes in LDS (64-byte rows, chunk c at c ^ ((r >> 2) & 3)) and are
+// converted when read (835 rows: gate/up 218 -> 196 us; 8192 rows 1570 ->
+// 1394), instead of passing through registers on their way in.
 // With fewer tiles than CUs (decode-sized M of 256 against a few thousand
 // columns) blocks split K (gridDim.y splits of kt_per K tiles) and write
 // fp32 partials in logical column space for the split-K epilogue kernel.
@@ -710,6 +737,7 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__
 constexpr int BG_BM = 256, BG_BN = 256, BG_BK = 64;
 constexpr int BG_THREADS = 512;
 constexpr int BG_TILE_BYTES = 256 * BG_BK * 2;  // one operand tile: 32 KiB
+constexpr int BG_HALF_BYTES = BG_TILE_BYTES / 2;
 
 __device__ __forceinline__ int bg_swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
@@ -723,13 +751,38 @@ struct GroupedArgs {
   int max_tiles, a_nrows, f32_out;
 };
 
+// One 16-byte-per-lane buffer load straight into LDS at byte address lds +
+// 16 lane (lds wave-uniform).  In assembly, so that the compiler does not
+// take every later LDS read to depend on it and drain all loads in flight:
+// the kernel counts its own loads (s_waitcnt vmcnt) instead.  The load
+// writes no register.
+__device__ __forceinline__ void bg_dma16(u32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void bg_wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void bg_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ u32x4_t bg_rsrc(const void *base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  return u32x4_t{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, bytes, 0x00020000u};
+}
+
 template <bool W8, bool GROUPED>
 __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restrict__ A, const void *__restrict__ W,
                                                          const float *__restrict__ wscale, uint16_t *__restrict__ out,
                                                          const uint16_t *__restrict__ res, float *__restrict__ part,
                                                          int M, int N, int K, int epi, int tiles_m, int tiles_n,
                                                          int per_xcd, int kt_per, GroupedArgs ga) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t bg_lds[];  // [2][A tile | W tile]
+  extern __shared__ __attribute__((aligned(16))) uint8_t bg_lds[];  // [2][A0 | A1 | W0 | W1]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;  // 128 rows of M, 64 columns of N
@@ -767,47 +820,52 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
 
   constexpr uint32_t WES = W8 ? 1u : 2u;  // bytes per W element
   const int a_nrows = GROUPED ? ga.a_nrows : M;
-  const buf_rsrc_t ra = make_rsrc(A, (int)min((size_t)a_nrows * K * 2, (size_t)0x7FFFFFFF));
-  const buf_rsrc_t rw = make_rsrc(Wt, (int)min((size_t)N * K * WES, (size_t)0x7FFFFFFF));
-  // DMA: wave w moves LDS rows [32 w, 32 w + 32) of both tiles, 8 rows
-  // (1 KiB) per instruction; lane l fills row 8 i + l / 8, physical chunk
-  // l % 8 with logical chunk bg_swz(row, l % 8).  Rows outside the operands
-  // point 2 GiB in, past every descriptor's range, so they load zeros.
-  uint32_t aoff[4], woff[4];
+  const uint32_t a_bytes = (uint32_t)min((size_t)a_nrows * K * 2, (size_t)0x7FFFFFFF);
+  const uint32_t w_bytes = (uint32_t)min((size_t)N * K * WES, (size_t)0x7FFFFFFF);
+  // Loads.  A half tile is 128 LDS rows: A half h holds rows wm 128 + 64 h +
+  // 0..63 of both wave rows, W half h columns wn 64 + 32 h + 0..31 of the four
+  // wave columns, so every wave reads each half once per K tile.  Wave w
+  // fills LDS rows 16 w .. 16 w + 15 of a half: two instructions of 8 rows x
+  // 128 bytes (8-bit W: one of 16 rows x 64 bytes); lane l writes 16-byte
+  // position l % 8 (l % 4) of its row with the logical chunk swizzled there.
+  // Rows outside the operands point 2 GiB in, past every descriptor's range,
+  // so they load zeros.
+  uint32_t aoff[2][2], woff[2][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = wave * 32 + i * 8 + (lane >> 3);
-    const int c = bg_swz(row, lane & 7);
-    int ar = row < mlim ? m0 + row : -1;
-    if constexpr (GROUPED)
-      if (ar >= 0 && ga.a_rows) ar = ga.a_rows[ar];
-    aoff[i] = ar >= 0 && ar < a_nrows ? ((uint32_t)ar * (uint32_t)K + (uint32_t)(c * 8)) * 2u : 0x80000000u;
-    const int wr = w_row_of(n0 + row, N, epi);
-    woff[i] = wr >= 0 ? ((uint32_t)wr * (uint32_t)K + (uint32_t)(c * 8)) * WES : 0x80000000u;
-  }
-  typedef __attribute__((address_space(3))) void lds_void;
-  // 8-bit weights come through registers: lane l of wave w holds the 8
-  // codes of row 32 w + 8 i + l / 8, logical chunk bg_swz(row, l % 8) (the
-  // same positions the DMA fills), converted to bf16 when written to LDS
-  u32x2_t wcodes[4];
-  auto dma = [&](int kt, int buf) {
-    uint8_t *base = bg_lds + buf * 2 * BG_TILE_BYTES + wave * 32 * 128;
-    const uint32_t kb = (uint32_t)kt * BG_BK * 2u;
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(base + i * 1024), 16, aoff[i] + kb, 0, 0, 0);
-      if constexpr (W8)
-        wcodes[i] = buf_ld_u32x2<0>(rw, (int)(woff[i] == 0x80000000u ? woff[i] : woff[i] + kb / 2u));
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + BG_TILE_BYTES + i * 1024), 16, woff[i] + kb,
-                                                 0, 0, 0);
+    for (int j = 0; j < 2; ++j) {
+      const int i = wave * 16 + j * 8 + (lane >> 3);  // LDS row of the half
+      const int c = bg_swz(i, lane & 7);
+      const int row = (i >> 6) * 128 + h * 64 + (i & 63);
+      int ar = row < mlim ? m0 + row : -1;
+      if constexpr (GROUPED)
+        if (ar >= 0 && ga.a_rows) ar = ga.a_rows[ar];
+      aoff[h][j] = ar >= 0 && ar < a_nrows ? ((uint32_t)ar * (uint32_t)K + (uint32_t)(c * 8)) * 2u : 0x80000000u;
+      if constexpr (!W8) {
+        const int wr = w_row_of(n0 + (i >> 5) * 64 + h * 32 + (i & 31), N, epi);
+        woff[h][j] = wr >= 0 ? ((uint32_t)wr * (uint32_t)K + (uint32_t)(c * 8)) * 2u : 0x80000000u;
+      } else if (j == 0) {
+        const int i8 = wave * 16 + (lane >> 2);
+        const int wr = w_row_of(n0 + (i8 >> 5) * 64 + h * 32 + (i8 & 31), N, epi);
+        woff[h][0] = wr >= 0 ? (uint32_t)wr * (uint32_t)K + (uint32_t)(((lane & 3) ^ ((i8 >> 2) & 3)) * 16) : 0x80000000u;
+      }
     }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)bg_lds;
+  auto dma_a = [&](int kt, int h) {  // (past the last K tile: an empty range, no traffic)
+    const u32x4_t r = bg_rsrc(A, kt < kt1 ? a_bytes : 0u);
+    const uint32_t kb = kt < kt1 ? (uint32_t)kt * (BG_BK * 2u) : 0u;
+    const uint32_t dst = lds0 + (uint32_t)(((kt - kt0) & 1) * 2 * BG_TILE_BYTES + h * BG_HALF_BYTES + wave * 2048);
+    bg_dma16(r, aoff[h][0], kb, dst);
+    bg_dma16(r, aoff[h][1], kb, dst + 1024);
   };
-  auto wstore = [&](int buf) {  // 8-bit weights: the converted W tile of the last dma into LDS
-    uint8_t *base = bg_lds + buf * 2 * BG_TILE_BYTES + BG_TILE_BYTES + wave * 32 * 128;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<u32x4_t *>(base + i * 1024 + lane * 16) = e4m3x8_to_bf16x8(wcodes[i]);
+  auto dma_w = [&](int kt, int h) {
+    const u32x4_t r = bg_rsrc(Wt, kt < kt1 ? w_bytes : 0u);
+    const uint32_t kb = kt < kt1 ? (uint32_t)kt * (BG_BK * WES) : 0u;
+    const uint32_t dst = lds0 + (uint32_t)(((kt - kt0) & 1) * 2 * BG_TILE_BYTES + BG_TILE_BYTES + h * BG_HALF_BYTES +
+                                           wave * (W8 ? 1024 : 2048));
+    bg_dma16(r, woff[h][0], kb, dst);
+    if constexpr (!W8) bg_dma16(r, woff[h][1], kb, dst + 1024);
   };
 
   f32x4_t acc[4][8];  // [W block jn][A block im]: rows n, cols m
@@ -816,38 +874,93 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+  // Operand reads: LDS row 16 i + lr of a half, for both 32-wide K steps.
+  // 8-bit W: a lane takes the 16 codes of chunk lg, so lane group lg holds k
+  // = 16 lg + 8 ks .. + 7 in step ks, and A is read in the same order.
   const int lr = lane & 15, lg = lane >> 4;
-  dma(kt0, 0);
-  if constexpr (W8) wstore(0);
-  __syncthreads();
-  for (int kt = kt0; kt < kt1; ++kt) {
-    const int buf = (kt - kt0) & 1;
-    if (kt + 1 < kt1) dma(kt + 1, buf ^ 1);
-    const uint8_t *sa = bg_lds + buf * 2 * BG_TILE_BYTES;
-    const uint8_t *sw = sa + BG_TILE_BYTES;
+  const int sw = (lr >> 1) & 7;
+  const uint32_t apos = (uint32_t)(lr * 128 + ((W8 ? 2 * lg : lg) ^ sw) * 16);
+  const uint32_t wpos = W8 ? (uint32_t)(lr * 64 + (lg ^ ((lr >> 2) & 3)) * 16) : apos;
+  constexpr uint32_t KSX = W8 ? 16u : 64u;  // position of step 1 = that of step 0 ^ KSX
+  uint32_t abase = (uint32_t)(wm * 64 * 128) + apos;
+  uint32_t wbase = (uint32_t)(BG_TILE_BYTES + wn * 32 * (W8 ? 64 : 128)) + wpos;
+  u32x4_t ax[4][2], ay[4][2];  // A halves 0 and 1: [16-row block][K step]
+  u32x4_t w0[2][2], w1[2][2];  // W halves
+  auto read_a = [&](uint32_t base, int h, u32x4_t (&f)[4][2]) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      u32x4_t af[8], wf[4];
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int r = wm * 128 + i * 16 + lr;
-        af[i] = *reinterpret_cast<const u32x4_t *>(sa + r * 128 + bg_swz(r, ks * 4 + lg) * 16);
+      for (int ks = 0; ks < 2; ++ks)
+        f[i][ks] = *reinterpret_cast<const u32x4_t *>(bg_lds + ((base ^ (ks ? KSX : 0u)) + h * BG_HALF_BYTES + i * 2048));
+  };
+  auto read_w = [&](uint32_t base, int h, u32x4_t (&f)[2][2]) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if constexpr (W8) {
+        const u32x4_t c = *reinterpret_cast<const u32x4_t *>(bg_lds + (base + h * BG_HALF_BYTES + j * 1024));
+        f[j][0] = e4m3x8_to_bf16x8(u32x2_t{c[0], c[1]});
+        f[j][1] = e4m3x8_to_bf16x8(u32x2_t{c[2], c[3]});
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+          f[j][ks] =
+              *reinterpret_cast<const u32x4_t *>(bg_lds + ((base ^ (ks ? KSX : 0u)) + h * BG_HALF_BYTES + j * 2048));
       }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = wn * 64 + j * 16 + lr;
-        wf[j] = *reinterpret_cast<const u32x4_t *>(sw + r * 128 + bg_swz(r, ks * 4 + lg) * 16);
-      }
-#pragma unroll
-      for (int jn = 0; jn < 4; ++jn)
-#pragma unroll
-        for (int im = 0; im < 8; ++im) acc[jn][im] = mfma16x16x32(wf[jn], af[im], acc[jn][im]);
     }
-    // the other buffer was last read in the previous step, before its barrier
-    if constexpr (W8)
-      if (kt + 1 < kt1) wstore(buf ^ 1);
-    __syncthreads();
+  };
+  auto products = [&](const u32x4_t (&wf)[2][2], const u32x4_t (&af)[4][2], int hw, int ha) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[hw * 2 + j][ha * 4 + i] = mfma16x16x32(wf[j][ks], af[i][ks], acc[hw * 2 + j][ha * 4 + i]);
+    bg_barrier();
+  };
+  constexpr int NW_ = W8 ? 1 : 2;  // load instructions of a W half (an A half has 2)
+  dma_a(kt0, 0);
+  dma_w(kt0, 0);
+  dma_w(kt0, 1);
+  dma_a(kt0, 1);
+  dma_a(kt0 + 1, 0);
+  dma_w(kt0 + 1, 0);
+  dma_w(kt0 + 1, 1);
+  bg_wait_loads<4 + 3 * NW_>();
+  bg_barrier();
+  read_a(abase, 0, ax);
+  if (wm == 1) bg_barrier();
+  for (int kt = kt0; kt < kt1; ++kt) {
+    read_w(wbase, 0, w0);
+    dma_a(kt + 1, 1);
+    bg_wait_loads<6 + 2 * NW_>();
+    bg_barrier();
+    products(w0, ax, 0, 0);
+
+    read_w(wbase, 1, w1);
+    dma_a(kt + 2, 0);
+    bg_wait_loads<6 + 2 * NW_>();
+    bg_barrier();
+    products(w1, ax, 1, 0);
+
+    read_a(abase, 1, ay);
+    dma_w(kt + 2, 0);
+    bg_wait_loads<4 + 3 * NW_>();
+    bg_barrier();
+    products(w1, ay, 1, 1);
+
+    abase ^= 2 * BG_TILE_BYTES;
+    wbase ^= 2 * BG_TILE_BYTES;
+    read_a(abase, 0, ax);
+    dma_w(kt + 2, 1);
+    bg_wait_loads<4 + 3 * NW_>();
+    bg_barrier();
+    products(w0, ay, 0, 1);
   }
+  bg_wait_loads<0>();
+  if (wm == 0) bg_barrier();
   if constexpr (W8) {  // the rows' scales, before any epilogue or partial
 #pragma unroll
     for (int jn = 0; jn < 4; ++jn) {
