@@ -13,24 +13,18 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-// bf16 bits <-> fp32.  Widening is exact; narrowing rounds to nearest even,
-// NaN maps to a quiet NaN.
+// bf16 bits <-> fp32.  Widening is exact; narrowing rounds to nearest even by
+// the hardware's packed conversion (one instruction for a pair; NaN stays a
+// quiet NaN).
 EB_DEV float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 EB_DEV float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 EB_DEV float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-EB_DEV uint32_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-EB_DEV uint32_t pack_bf16x2(float lo, float hi) { return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16); }
-// The same rounding (nearest even) by the hardware's packed conversion, one
-// instruction for the pair.
-EB_DEV uint32_t bf16_pair_rne(float lo, float hi) {
+EB_DEV uint32_t pack_bf16x2(float lo, float hi) {
   typedef float f32x2_v __attribute__((ext_vector_type(2)));
   const f32x2_v f = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
 }
+EB_DEV uint32_t f32_to_bf16_bits(float f) { return pack_bf16x2(f, 0.f); }
 
 // DPP row controls (a "row" is 16 lanes).
 #define EB_DPP_QUAD_XOR1 0xB1   // quad_perm [1,0,3,2]
@@ -93,6 +87,16 @@ EB_DEV u32x4_t buf_ld_u32x4(buf_rsrc_t r, int off) {
 template <int AUX = 0>
 EB_DEV u32x2_t buf_ld_u32x2(buf_rsrc_t r, int off) {
   return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX));
+}
+
+// 8- and 16-byte stores at byte offset `off`; stores past the range are dropped.
+EB_DEV void buf_st_b64(buf_rsrc_t r, uint32_t off, u32x2_t v) {
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, (int)off, 0, 0);
+}
+EB_DEV void buf_st_b128(buf_rsrc_t r, uint32_t off, f32x4_t v) {
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, (int)off, 0, 0);
 }
 
 EB_DEV bf16x8_t as_bf16x8(u32x4_t v) { return __builtin_bit_cast(bf16x8_t, v); }

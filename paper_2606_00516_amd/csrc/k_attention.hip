@@ -441,7 +441,7 @@ __device__ __forceinline__ void mdec_page_update(const uint8_t *slot, const u32x
   mrun = mnew;
   // P^T (keys 4 g .. 4 g + 3 of this lane's head) as the B operand of the
   // 16x16x16 product
-  const u32x2_t pt = {bf16_pair_rne(pr[0], pr[1]), bf16_pair_rne(pr[2], pr[3])};
+  const u32x2_t pt = {pack_bf16x2(pr[0], pr[1]), pack_bf16x2(pr[2], pr[3])};
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks) {
     const u32x4_t vv = dims8(rowp + Tr::BLK, ks);
@@ -1050,8 +1050,8 @@ __device__ __forceinline__ void prefill_item(const uint16_t *__restrict__ qkv, i
           p4[j] = fast_exp2(fmaf(sc[i][kb][j], qscale, neg));
           l += p4[j];
         }
-        pk[i][kb][0] = bf16_pair_rne(p4[0], p4[1]);
-        pk[i][kb][1] = bf16_pair_rne(p4[2], p4[3]);
+        pk[i][kb][0] = pack_bf16x2(p4[0], p4[1]);
+        pk[i][kb][1] = pack_bf16x2(p4[2], p4[3]);
       }
       lrun[i] = l;
       mrun[i] = mx;
@@ -1340,7 +1340,7 @@ __device__ __forceinline__ void prefill_item32(const uint16_t *__restrict__ qkv,
       for (int pr = 0; pr < 8; ++pr) {
         const float p0 = fast_exp2(fmaf(sc[kb][2 * pr], qscale, neg));
         const float p1 = fast_exp2(fmaf(sc[kb][2 * pr + 1], qscale, neg));
-        pk[kb][pr] = bf16_pair_rne(p0, p1);
+        pk[kb][pr] = pack_bf16x2(p0, p1);
         l = dot2_bf16(pk[kb][pr], 0x3F803F80u, l);  // + both values, (1, 1) in bf16
       }
     // (a row whose max was still -inf has nothing accumulated to rescale)
@@ -1601,7 +1601,7 @@ __device__ __forceinline__ void prefill_item32_dma(const uint16_t *__restrict__ 
       for (int pr = 0; pr < 8; ++pr) {
         const float p0 = fast_exp2(fmaf(sc[kb][2 * pr], qscale, neg));
         const float p1 = fast_exp2(fmaf(sc[kb][2 * pr + 1], qscale, neg));
-        pk[kb][pr] = bf16_pair_rne(p0, p1);
+        pk[kb][pr] = pack_bf16x2(p0, p1);
         l = dot2_bf16(pk[kb][pr], 0x3F803F80u, l);
       }
     // (the test on l, true for every finite sum, ties the branch below to

@@ -38,7 +38,8 @@ __host__ __device__ static inline int logical_cols(int N, int epi) {
   return ((F + 31) / 32) * 64;
 }
 
-__device__ __forceinline__ float silu_f(float g) { return g / (1.0f + __expf(-g)); }
+// (the reciprocal instruction is good to one unit in the last place of fp32)
+__device__ __forceinline__ float silu_f(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 // 8-bit weights: the fp32 sums of logical columns c .. c + 3 (one W row
 // each, consecutive within a column group) times their rows' scales.
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(const uint16_t *__restrict_
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          av[e] = bf16_pair_rne(bf16_lo(ar[j][e]) * bf16_lo(gr[e]), bf16_hi(ar[j][e]) * bf16_hi(gr[e]));
+          av[e] = pack_bf16x2(bf16_lo(ar[j][e]) * bf16_lo(gr[e]), bf16_hi(ar[j][e]) * bf16_hi(gr[e]));
       }
       *reinterpret_cast<u32x4_t *>(b + (SW_BN + r0 + 16 * j) * SK_ROWB + ch * 16) = av;
     }
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(256) void k_gemm_skinny_packed(const uint16_t *__re
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          av[e] = bf16_pair_rne(bf16_lo(aa[j][e]) * bf16_lo(ga[e]), bf16_hi(aa[j][e]) * bf16_hi(ga[e]));
+          av[e] = pack_bf16x2(bf16_lo(aa[j][e]) * bf16_lo(ga[e]), bf16_hi(aa[j][e]) * bf16_hi(ga[e]));
       }
       *reinterpret_cast<u32x4_t *>(b + (r0 + 16 * j) * SK_ROWB + ch * 16) = av;
     }
@@ -776,11 +777,11 @@ __device__ __forceinline__ u32x4_t bg_rsrc(const void *base, uint32_t bytes) {
   return u32x4_t{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, bytes, 0x00020000u};
 }
 
-template <bool W8, bool GROUPED>
+template <int epi, bool W8, bool GROUPED>
 __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restrict__ A, const void *__restrict__ W,
                                                          const float *__restrict__ wscale, uint16_t *__restrict__ out,
                                                          const uint16_t *__restrict__ res, float *__restrict__ part,
-                                                         int M, int N, int K, int epi, int tiles_m, int tiles_n,
+                                                         int M, int N, int K, int tiles_m, int tiles_n,
                                                          int per_xcd, int kt_per, GroupedArgs ga) {
   extern __shared__ __attribute__((aligned(16))) uint8_t bg_lds[];  // [2][A0 | A1 | W0 | W1]
   const int lane = threadIdx.x & 63;
@@ -790,30 +791,33 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
   // block b works on tile (b % 8) * per_xcd + b / 8: each XCD walks its own
   // contiguous run of the (grouped) tile order and its L2 keeps the shared
   // A and W panels.
-  int m0, n0, mlim;  // first row, first logical column, rows of the tile in use
-  const void *Wt = W;
+  int total = tiles_m * tiles_n;
   if constexpr (GROUPED) {
-    const int rt = blockIdx.x / tiles_n;
-    if (rt >= __builtin_amdgcn_readfirstlane(*ga.n_tiles)) return;
+    total = __builtin_amdgcn_readfirstlane(*ga.n_tiles) * tiles_n;
+    per_xcd = (total + 7) / 8;
+  }
+  const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (blockIdx.x / 8 >= per_xcd || t >= total) return;
+  int m0, n0, mlim;  // first row, first logical column, rows of the tile in use
+  const uint8_t *Wt = static_cast<const uint8_t *>(W);
+  if constexpr (GROUPED) {
+    const int rt = t / tiles_n;
     const int e = __builtin_amdgcn_readfirstlane(ga.tiles[rt]);
     m0 = __builtin_amdgcn_readfirstlane(ga.tiles[ga.max_tiles + rt]);
     mlim = __builtin_amdgcn_readfirstlane(ga.tiles[2 * ga.max_tiles + rt]);
-    n0 = (blockIdx.x % tiles_n) * BG_BN;
-    Wt = static_cast<const uint16_t *>(W) + (size_t)e * N * K;
+    n0 = (t - rt * tiles_n) * BG_BN;
+    Wt += (size_t)e * N * K * 2;
   } else {
-    const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (t >= tiles_m * tiles_n) return;
     const int group = 8;
     const int per_group = group * tiles_m;
     const int gidx = t / per_group;
     const int first_n = gidx * group;
     const int gsz = min(group, tiles_n - first_n);
     const int inb = t - gidx * per_group;
-    const int tn = first_n + inb % gsz;
     const int tm = inb / gsz;
+    n0 = (first_n + inb - tm * gsz) * BG_BN;
     m0 = tm * BG_BM;
-    n0 = tn * BG_BN;
-    mlim = M - m0;
+    mlim = min(BG_BM, M - m0);
   }
   const int split = blockIdx.y;
   const int kt0 = split * kt_per, kt1 = min(K / BG_BK, kt0 + kt_per);
@@ -832,38 +836,40 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
   // so they load zeros.
   uint32_t aoff[2][2], woff[2][2];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int i = wave * 16 + j * 8 + (lane >> 3);  // LDS row of the half
-      const int c = bg_swz(i, lane & 7);
       const int row = (i >> 6) * 128 + h * 64 + (i & 63);
       int ar = row < mlim ? m0 + row : -1;
       if constexpr (GROUPED)
         if (ar >= 0 && ga.a_rows) ar = ga.a_rows[ar];
-      aoff[h][j] = ar >= 0 && ar < a_nrows ? ((uint32_t)ar * (uint32_t)K + (uint32_t)(c * 8)) * 2u : 0x80000000u;
-      if constexpr (!W8) {
-        const int wr = w_row_of(n0 + (i >> 5) * 64 + h * 32 + (i & 31), N, epi);
-        woff[h][j] = wr >= 0 ? ((uint32_t)wr * (uint32_t)K + (uint32_t)(c * 8)) * 2u : 0x80000000u;
-      } else if (j == 0) {
-        const int i8 = wave * 16 + (lane >> 2);
-        const int wr = w_row_of(n0 + (i8 >> 5) * 64 + h * 32 + (i8 & 31), N, epi);
-        woff[h][0] = wr >= 0 ? (uint32_t)wr * (uint32_t)K + (uint32_t)(((lane & 3) ^ ((i8 >> 2) & 3)) * 16) : 0x80000000u;
-      }
+      aoff[h][j] = ar >= 0 && ar < a_nrows ? ((uint32_t)ar * (uint32_t)K + (uint32_t)(bg_swz(i, lane & 7) * 8)) * 2u
+                                           : 0x80000000u;
     }
+#pragma unroll
+    for (int j = 0; j < (W8 ? 1 : 2); ++j) {
+      const int i = W8 ? wave * 16 + (lane >> 2) : wave * 16 + j * 8 + (lane >> 3);
+      const int wr = w_row_of(n0 + (i >> 5) * 64 + h * 32 + (i & 31), N, epi);
+      const int cb = (W8 ? (lane & 3) ^ ((i >> 2) & 3) : bg_swz(i, lane & 7)) * 16;
+      woff[h][j] = wr >= 0 ? (uint32_t)wr * (uint32_t)K * WES + (uint32_t)cb : 0x80000000u;
+    }
+  }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)bg_lds;
-  auto dma_a = [&](int kt, int h) {  // (past the last K tile: an empty range, no traffic)
+  // half h of K tile kt into the buffer at dst_buf (past the last K tile: an
+  // empty range, no traffic)
+  auto dma_a = [&](int kt, int h, uint32_t dst_buf) {
     const u32x4_t r = bg_rsrc(A, kt < kt1 ? a_bytes : 0u);
     const uint32_t kb = kt < kt1 ? (uint32_t)kt * (BG_BK * 2u) : 0u;
-    const uint32_t dst = lds0 + (uint32_t)(((kt - kt0) & 1) * 2 * BG_TILE_BYTES + h * BG_HALF_BYTES + wave * 2048);
+    const uint32_t dst = lds0 + dst_buf + (uint32_t)(h * BG_HALF_BYTES + wave * 2048);
     bg_dma16(r, aoff[h][0], kb, dst);
     bg_dma16(r, aoff[h][1], kb, dst + 1024);
   };
-  auto dma_w = [&](int kt, int h) {
+  auto dma_w = [&](int kt, int h, uint32_t dst_buf) {
     const u32x4_t r = bg_rsrc(Wt, kt < kt1 ? w_bytes : 0u);
     const uint32_t kb = kt < kt1 ? (uint32_t)kt * (BG_BK * WES) : 0u;
-    const uint32_t dst = lds0 + (uint32_t)(((kt - kt0) & 1) * 2 * BG_TILE_BYTES + BG_TILE_BYTES + h * BG_HALF_BYTES +
-                                           wave * (W8 ? 1024 : 2048));
+    const uint32_t dst =
+        lds0 + dst_buf + (uint32_t)(BG_TILE_BYTES + h * BG_HALF_BYTES + wave * (W8 ? 1024 : 2048));
     bg_dma16(r, woff[h][0], kb, dst);
     if constexpr (!W8) bg_dma16(r, woff[h][1], kb, dst + 1024);
   };
@@ -921,118 +927,134 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
     bg_barrier();
   };
   constexpr int NW_ = W8 ? 1 : 2;  // load instructions of a W half (an A half has 2)
-  dma_a(kt0, 0);
-  dma_w(kt0, 0);
-  dma_w(kt0, 1);
-  dma_a(kt0, 1);
-  dma_a(kt0 + 1, 0);
-  dma_w(kt0 + 1, 0);
-  dma_w(kt0 + 1, 1);
+  constexpr uint32_t BUF = 2 * BG_TILE_BYTES;
+  uint32_t buf = 0;  // LDS buffer of the K tile in use
+  dma_a(kt0, 0, 0);
+  dma_w(kt0, 0, 0);
+  dma_w(kt0, 1, 0);
+  dma_a(kt0, 1, 0);
+  dma_a(kt0 + 1, 0, BUF);
+  dma_w(kt0 + 1, 0, BUF);
+  dma_w(kt0 + 1, 1, BUF);
   bg_wait_loads<4 + 3 * NW_>();
   bg_barrier();
   read_a(abase, 0, ax);
   if (wm == 1) bg_barrier();
   for (int kt = kt0; kt < kt1; ++kt) {
     read_w(wbase, 0, w0);
-    dma_a(kt + 1, 1);
+    dma_a(kt + 1, 1, buf ^ BUF);
     bg_wait_loads<6 + 2 * NW_>();
     bg_barrier();
     products(w0, ax, 0, 0);
 
     read_w(wbase, 1, w1);
-    dma_a(kt + 2, 0);
+    dma_a(kt + 2, 0, buf);
     bg_wait_loads<6 + 2 * NW_>();
     bg_barrier();
     products(w1, ax, 1, 0);
 
     read_a(abase, 1, ay);
-    dma_w(kt + 2, 0);
+    dma_w(kt + 2, 0, buf);
     bg_wait_loads<4 + 3 * NW_>();
     bg_barrier();
     products(w1, ay, 1, 1);
 
-    abase ^= 2 * BG_TILE_BYTES;
-    wbase ^= 2 * BG_TILE_BYTES;
+    abase ^= BUF;
+    wbase ^= BUF;
     read_a(abase, 0, ax);
-    dma_w(kt + 2, 1);
+    dma_w(kt + 2, 1, buf);
     bg_wait_loads<4 + 3 * NW_>();
     bg_barrier();
     products(w0, ay, 0, 1);
+    buf ^= BUF;
   }
   bg_wait_loads<0>();
   if (wm == 0) bg_barrier();
+
+  // Epilogue: lane holds out[m][n .. n + 3] with m = m0 + wm 128 + 16 im + lr,
+  // n = n0 + wn 64 + 16 jn + 4 lg (N and F are multiples of 4, so a group of
+  // 4 columns is either wholly inside or wholly outside).  Rows and columns
+  // outside are dropped by the buffer range over the tile's rows (columns
+  // point 2 GiB in), so there is no branch per store and the residual's
+  // loads go out sixteen at a time.
+  const int ncols = logical_cols(N, epi);
+  const int nl = n0 + wn * 64 + lg * 4;
+  const uint32_t row = wm * 128 + lr;  // of the tile, at im = 0
+  auto at = [&](int ld, int es, int col, int lim) -> uint32_t {  // byte of (row, col) in a tile of ld columns
+    return col < lim ? (row * (uint32_t)ld + (uint32_t)col) * (uint32_t)es : 0x80000000u;
+  };
   if constexpr (W8) {  // the rows' scales, before any epilogue or partial
 #pragma unroll
-    for (int jn = 0; jn < 4; ++jn) {
-      const int n = n0 + wn * 64 + jn * 16 + lg * 4;
-      if (n < logical_cols(N, epi)) {
+    for (int jn = 0; jn < 4; ++jn)
+      if (nl + jn * 16 < ncols) {
 #pragma unroll
-        for (int im = 0; im < 8; ++im) acc[jn][im] = row_scaled(acc[jn][im], wscale, n, N, epi);
+        for (int im = 0; im < 8; ++im) acc[jn][im] = row_scaled(acc[jn][im], wscale, nl + jn * 16, N, epi);
       }
-    }
   }
-
-  // epilogue: lane holds out[m][n .. n+3] with m = m0 + wm*128 + 16 im + lr,
-  // n = n0 + wn*64 + 16 jn + 4 lg (N and F are multiples of 4, so a group of
-  // 4 columns is either wholly inside or wholly outside)
-  if (part) {  // split-K partial, logical column space
-    const int ncols = logical_cols(N, epi);
+  if (part || (GROUPED && ga.f32_out)) {  // fp32: a split-K partial (logical column space), or the product itself
+    float *base = part ? part + ((size_t)split * M + m0) * ncols : reinterpret_cast<float *>(out) + (size_t)m0 * N;
+    const buf_rsrc_t ro = make_rsrc(base, mlim * ncols * 4);
 #pragma unroll
     for (int jn = 0; jn < 4; ++jn) {
-      const int n = n0 + wn * 64 + jn * 16 + lg * 4;
+      const uint32_t o = at(ncols, 4, nl + jn * 16, ncols);
 #pragma unroll
-      for (int im = 0; im < 8; ++im) {
-        const int m = m0 + wm * 128 + im * 16 + lr;
-        if (m - m0 < mlim && n < ncols) *reinterpret_cast<f32x4_t *>(part + ((size_t)split * M + m) * ncols + n) = acc[jn][im];
-      }
+      for (int im = 0; im < 8; ++im) buf_st_b128(ro, o + (uint32_t)im * 64u * (uint32_t)ncols, acc[jn][im]);
     }
     return;
   }
-  if (epi == EPI_SILU_MUL) {
+  if constexpr (epi == EPI_SILU_MUL) {
     // the wave's 64 columns are one [32 gate | 32 up] group: blocks jn and
     // jn + 2 pair up
     const int F = N >> 1;
+    const buf_rsrc_t ro = make_rsrc(out + (size_t)m0 * F, mlim * F * 2);
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj) {
-      const int f = ((n0 + wn * 64) >> 1) + jj * 16 + lg * 4;
+      const uint32_t o = at(F, 2, ((n0 + wn * 64) >> 1) + jj * 16 + lg * 4, F);
 #pragma unroll
       for (int im = 0; im < 8; ++im) {
-        const int m = m0 + wm * 128 + im * 16 + lr;
-        if (m - m0 < mlim && f < F) {
-          const f32x4_t gv = acc[jj][im], uv = acc[jj + 2][im];
-          u32x2_t w = {pack_bf16x2(silu_f(gv[0]) * uv[0], silu_f(gv[1]) * uv[1]),
-                       pack_bf16x2(silu_f(gv[2]) * uv[2], silu_f(gv[3]) * uv[3])};
-          *reinterpret_cast<u32x2_t *>(out + (size_t)m * F + f) = w;
-        }
+        const f32x4_t gv = acc[jj][im], uv = acc[jj + 2][im];
+        buf_st_b64(ro, o + (uint32_t)im * 32u * (uint32_t)F,
+                   u32x2_t{pack_bf16x2(silu_f(gv[0]) * uv[0], silu_f(gv[1]) * uv[1]),
+                           pack_bf16x2(silu_f(gv[2]) * uv[2], silu_f(gv[3]) * uv[3])});
+        if (im % 2) __builtin_amdgcn_sched_barrier(0);
       }
     }
     return;
   }
+  const buf_rsrc_t ro = make_rsrc(out + (size_t)m0 * N, mlim * N * 2);
+  uint32_t o[4];
 #pragma unroll
-  for (int jn = 0; jn < 4; ++jn) {
-    const int n = n0 + wn * 64 + jn * 16 + lg * 4;
+  for (int jn = 0; jn < 4; ++jn) o[jn] = at(N, 2, nl + jn * 16, N);
+  if constexpr (epi == EPI_RESIDUAL) {
+    const buf_rsrc_t rr = make_rsrc(res + (size_t)m0 * N, mlim * N * 2);
 #pragma unroll
-    for (int im = 0; im < 8; ++im) {
-      const int m = m0 + wm * 128 + im * 16 + lr;
-      if (m - m0 < mlim && n < N) {
-        f32x4_t v = acc[jn][im];
-        if constexpr (GROUPED) {
-          if (ga.f32_out) {
-            *reinterpret_cast<f32x4_t *>(reinterpret_cast<float *>(out) + (size_t)m * N + n) = v;
-            continue;
-          }
-        }
-        if (epi == EPI_RESIDUAL) {
-          const u32x2_t r = *reinterpret_cast<const u32x2_t *>(res + (size_t)m * N + n);
-          v[0] += bf16_lo(r[0]);
-          v[1] += bf16_hi(r[0]);
-          v[2] += bf16_lo(r[1]);
-          v[3] += bf16_hi(r[1]);
-        }
-        u32x2_t w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-        *reinterpret_cast<u32x2_t *>(out + (size_t)m * N + n) = w;
-      }
+    for (int j2 = 0; j2 < 4; j2 += 2) {  // (half of them at a time: registers)
+      u32x2_t r[2][8];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int im = 0; im < 8; ++im)
+          r[j][im] = buf_ld_u32x2<0>(rr, (int)(o[j2 + j] + (uint32_t)im * 32u * (uint32_t)N));
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int im = 0; im < 8; ++im)
+          acc[j2 + j][im] +=
+              f32x4_t{bf16_lo(r[j][im][0]), bf16_hi(r[j][im][0]), bf16_lo(r[j][im][1]), bf16_hi(r[j][im][1])};
+      __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  // (unknown to the compiler from here: it would keep all 32 addresses of the
+  // residual's loads in registers for the stores, and spill)
+#pragma unroll
+  for (int jn = 0; jn < 4; ++jn) asm volatile("" : "+v"(o[jn]));
+#pragma unroll
+  for (int im = 0; im < 8; ++im) {
+#pragma unroll
+    for (int jn = 0; jn < 4; ++jn)
+      buf_st_b64(ro, o[jn] + (uint32_t)im * 32u * (uint32_t)N,
+                 u32x2_t{pack_bf16x2(acc[jn][im][0], acc[jn][im][1]), pack_bf16x2(acc[jn][im][2], acc[jn][im][3])});
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -1309,7 +1331,9 @@ GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8) {
   const int ncols = logical_cols(N, epi);
   // the big kernel addresses W through a 32-bit buffer range; A is cut into
   // row chunks that each fit one (launch_gemm)
-  const bool fits = (size_t)N * K * 2 < ((size_t)1 << 31) && (size_t)BG_BM * K * 2 < ((size_t)1 << 31);
+  // (and a tile's rows of the output through another)
+  const bool fits = (size_t)N * K * 2 < ((size_t)1 << 31) && (size_t)BG_BM * K * 2 < ((size_t)1 << 31) &&
+                    (size_t)BG_BM * ncols * 4 < ((size_t)1 << 31);
   // 256 x 256 tiles once the grid covers at least half the CUs
   const long big_tiles = (long)((M + BG_BM - 1) / BG_BM) * ((ncols + BG_BN - 1) / BG_BN);
   if (K % BG_BK == 0 && N % 8 == 0 && fits && M >= 256) {
@@ -1359,6 +1383,18 @@ hipError_t pack_weight(const uint16_t *W, uint16_t *P, int N, int K, hipStream_t
   return hipGetLastError();
 }
 
+// One 256 x 256 launch: the kernel of the epilogue and weight type.
+template <bool W8, bool GROUPED>
+static void launch_big(dim3 grid, hipStream_t st, const uint16_t *A, const void *W, const float *wscale, uint16_t *out,
+                       const uint16_t *res, float *part, int M, int N, int K, int epi, int tm, int tn, int per_xcd,
+                       int kt_per, const GroupedArgs &ga) {
+  auto k = epi == EPI_SILU_MUL               ? k_gemm_big<EPI_SILU_MUL, W8, GROUPED>
+           : epi == EPI_RESIDUAL && !GROUPED ? k_gemm_big<GROUPED ? EPI_STORE : EPI_RESIDUAL, W8, GROUPED>
+                                             : k_gemm_big<EPI_STORE, W8, GROUPED>;
+  hipLaunchKernelGGL(k, grid, dim3(BG_THREADS), 4 * BG_TILE_BYTES, st, A, W, wscale, out, res, part, M, N, K, tm, tn,
+                     per_xcd, kt_per, ga);
+}
+
 hipError_t launch_gemm(const GemmPlan &p, const uint16_t *A, const void *W, const float *wscale, uint16_t *out,
                        const uint16_t *res, int M, int N, int K, int epi, void *ws, hipStream_t st, NormFuse *nf,
                        const uint16_t *Wp) {
@@ -1394,12 +1430,9 @@ hipError_t launch_gemm(const GemmPlan &p, const uint16_t *A, const void *W, cons
       const int tm = (M + BG_BM - 1) / BG_BM, tn = (ncols + BG_BN - 1) / BG_BN;
       const int per_xcd = (tm * tn + 7) / 8;
       float *part = reinterpret_cast<float *>(ws);
-      if (w8)
-        hipLaunchKernelGGL((k_gemm_big<true, false>), dim3(8 * per_xcd, p.splits), dim3(BG_THREADS), 4 * BG_TILE_BYTES, st, A,
-                           W, wscale, out, res, part, M, N, K, epi, tm, tn, per_xcd, p.kt_per, GroupedArgs{});
-      else
-        hipLaunchKernelGGL((k_gemm_big<false, false>), dim3(8 * per_xcd, p.splits), dim3(BG_THREADS), 4 * BG_TILE_BYTES, st, A,
-                           W, wscale, out, res, part, M, N, K, epi, tm, tn, per_xcd, p.kt_per, GroupedArgs{});
+      auto launch = w8 ? launch_big<true, false> : launch_big<false, false>;
+      launch(dim3(8 * per_xcd, p.splits), st, A, W, wscale, out, res, part, M, N, K, epi, tm, tn, per_xcd, p.kt_per,
+             GroupedArgs{});
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       return finish_splitk(part, p.splits, out, res, M, N, epi, nf, st);
@@ -1412,16 +1445,9 @@ hipError_t launch_gemm(const GemmPlan &p, const uint16_t *A, const void *W, cons
       const int mc = M - m0 < chunk ? M - m0 : chunk;
       const int tm = (mc + BG_BM - 1) / BG_BM, tn = (ncols + BG_BN - 1) / BG_BN;
       const int per_xcd = (tm * tn + 7) / 8;
-      if (w8)
-        hipLaunchKernelGGL((k_gemm_big<true, false>), dim3(8 * per_xcd), dim3(BG_THREADS), 4 * BG_TILE_BYTES, st,
-                           A + (size_t)m0 * K, W, wscale, out + (size_t)m0 * out_cols,
-                           res ? res + (size_t)m0 * N : nullptr, nullptr, mc, N, K, epi, tm, tn, per_xcd, K / BG_BK,
-                           GroupedArgs{});
-      else
-        hipLaunchKernelGGL((k_gemm_big<false, false>), dim3(8 * per_xcd), dim3(BG_THREADS), 4 * BG_TILE_BYTES, st,
-                           A + (size_t)m0 * K, W, wscale, out + (size_t)m0 * out_cols,
-                           res ? res + (size_t)m0 * N : nullptr, nullptr, mc, N, K, epi, tm, tn, per_xcd, K / BG_BK,
-                           GroupedArgs{});
+      auto launch = w8 ? launch_big<true, false> : launch_big<false, false>;
+      launch(dim3(8 * per_xcd), st, A + (size_t)m0 * K, W, wscale, out + (size_t)m0 * out_cols,
+             res ? res + (size_t)m0 * N : nullptr, nullptr, mc, N, K, epi, tm, tn, per_xcd, K / BG_BK, GroupedArgs{});
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -1464,9 +1490,9 @@ hipError_t launch_gemm_grouped_big(const uint16_t *A, int a_nrows, const int32_t
   if (K % BG_BK) return hipErrorInvalidValue;
   const int tiles_n = (logical_cols(N, epi) + BG_BN - 1) / BG_BN;
   const GroupedArgs ga{a_rows, tiles, n_tiles, max_tiles, a_nrows, f32_out ? 1 : 0};
-  hipLaunchKernelGGL((k_gemm_big<false, true>), dim3((unsigned)max_tiles * (unsigned)tiles_n), dim3(BG_THREADS),
-                     4 * BG_TILE_BYTES, st, A, W, nullptr, static_cast<uint16_t *>(out), nullptr, nullptr, 0, N, K,
-                     epi, 0, tiles_n, 0, K / BG_BK, ga);
+  const unsigned grid = ((unsigned)max_tiles * (unsigned)tiles_n + 7) / 8 * 8;
+  launch_big<false, true>(dim3(grid), st, A, W, nullptr, static_cast<uint16_t *>(out), nullptr, nullptr, 0, N, K, epi, 0,
+                          tiles_n, 0, K / BG_BK, ga);
   return hipGetLastError();
 }
 
