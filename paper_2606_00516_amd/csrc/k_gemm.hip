@@ -2,15 +2,15 @@
 // W [N, K] weights, both K-contiguous bf16, fp32 accumulation on the
 // 16x16x32 bf16 MFMA.
 //
-//  * skinny: decode-sized batches (up to 256 rows, 64-row x 128-column
-//    tiles, one block per CU).  The product is bound by streaming W from HBM
-//    once: tiles stage W and A through LDS in 128-wide K slices read as
-//    whole 256-byte rows, the 4 waves of a block own 32 columns each, the
-//    row blocks of a column tile run side by side on one XCD so W comes from
-//    HBM once, and blocks may further split K, with a small reduction kernel
-//    applying the epilogue.
-//  * tiled: larger M.  128x128 output tiles, K tiles of 64 double-buffered in
-//    LDS, 4 waves each owning a 64x64 sub-tile.
+//  * stream: decode-sized batches (up to 256 rows, all of them in one block
+//    of 128 columns, one block per CU).  The product is bound by streaming W
+//    from HBM once: W and A go straight into an LDS ring that fills the CU,
+//    all but one stage of it in flight, and blocks may further split K, with
+//    a small reduction kernel applying the epilogue.  Up to 64 rows, W may
+//    come from a fragment-packed copy straight into registers.
+//  * big: 256 x 256 tiles, larger M.
+//  * tiled: what neither takes.  128x128 output tiles, K tiles of 64
+//    double-buffered in LDS, 4 waves each owning a 64x64 sub-tile.
 //
 // Epilogues: store; + residual; SiLU(gate) * up.  For SiLU the columns are
 // processed in groups of 64 = 32 gate rows of W followed by the 32 matching
@@ -50,10 +50,43 @@ __device__ __forceinline__ f32x4_t row_scaled(f32x4_t v, const float *__restrict
   return v * s;
 }
 
+// One 16-byte-per-lane buffer load straight into LDS at byte address lds +
+// 16 lane (lds wave-uniform).  In assembly, so that the compiler does not
+// take every later LDS read to depend on it and drain all loads in flight:
+// the kernel counts its own loads (s_waitcnt vmcnt) instead.  The load
+// writes no register.
+__device__ __forceinline__ void dma_lds16(u32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory", "m0");
+}
+// The same with 4 bytes per lane (256 bytes per instruction).
+__device__ __forceinline__ void dma_lds4(u32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wave_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ u32x4_t raw_rsrc(const void *base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  return u32x4_t{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, bytes, 0x00020000u};
+}
+
 // ===========================================================================
-// skinny
+// weight streaming from a fragment-packed copy, and the tile constants that the
+// grouped kernel shares
 // ===========================================================================
-constexpr int SK_BN = 64;                // logical columns per block
+constexpr int SK_BN = 64;                // logical columns per block (grouped)
 constexpr int SK_BM = 64;                // rows per block
 constexpr int SK_KC = 128;               // K per stage
 constexpr int SK_ROWB = SK_KC * 2 + 16;  // LDS bytes per tile row (padded)
@@ -64,238 +97,27 @@ constexpr int SK_LDS = 2 * (SK_BN + SK_BM) * SK_ROWB;
 // and its up partner (32 apart) land in the same wave.
 __device__ __forceinline__ int sk_col(int w, int j) { return j < 8 ? 8 * w + j : 32 + 8 * w + (j - 8); }
 
-// The weight-streaming kernel's block is 128 logical columns x 64 rows, one
-// block per CU.  W and A are staged through LDS in 128-wide K slices (each
-// load instruction reads 4 rows x 256 contiguous bytes, so a wave's loads
-// touch few pages), and each of the 4 waves owns 32 columns: per K step of
-// 32 it reads 2 W and 4 A fragments from LDS for 8 products, so the LDS
-// carries 3.5 bytes per weight byte (staging writes included) where a
-// 64-column block with 16 columns per wave carried 7.
-constexpr int SW_BN = 128;                                 // logical columns per block
-constexpr int SW_LDS = 2 * (SW_BN + SK_BM) * SK_ROWB;      // two stages of [128 W rows + 64 A rows]
+// The packed weight-streaming kernel's block is 128 logical columns x 64
+// rows, one block per CU; each of the 4 waves owns 32 columns.
+constexpr int SW_BN = 128;     // logical columns per block
+constexpr int kPackedMaxRows = SK_BM;
+
+// Where column tile ct of nct starts its walk over a K range of n 128-wide
+// steps that no other block shares (it wraps around).  Blocks that all start
+// at the first column read the same K offset of rows a power of two apart,
+// and those addresses meet on few memory channels; an eighth of the range
+// apart per XCD they spread, and the blocks of one XCD still share A's
+// stages in its L2.  Gate/up at 64 rows (W 28672 x 4096): 51.5 -> 43.0 us on
+// the row-major bf16 matrix, 31.8 -> 28.4 on 8-bit codes; split K ranges start
+// apart by themselves (down: no change).  The order depends on the column
+// tile alone, so a row's sums do not depend on the batch.
+__device__ __forceinline__ int k_start(int ct, int nct, int n) { return ct * 8 / nct * n / 8; }
 
 // Block-local logical column of row lr (0..15) of wave w's column fragment
 // f (0, 1): wave w takes half w % 2 of SiLU group w / 2, fragment 0 its 16
 // gate columns and fragment 1 their 16 up partners (32 further), so a lane
 // holds a gate sum and its partner.
 __device__ __forceinline__ int sw_col(int w, int f, int lr) { return (w >> 1) * 64 + f * 32 + (w & 1) * 16 + lr; }
-
-// PRENORM (split-K partials only): A holds the rows x of an RMSNorm that
-// precedes the product.  The kernel stages bf16(x * gamma) instead of A and
-// the blocks of the first column tile write each row's partial sum of
-// squares over their K range to ssq[split][M]; the row scale
-// 1 / sqrt(mean(x^2) + eps) is applied to the summed partials by the
-// consumer (RMSNorm(x) g W^T = inv * ((x g) W^T)).
-template <bool W8, bool PRENORM = false>
-__global__ __launch_bounds__(256) void k_gemm_skinny(const uint16_t *__restrict__ A, const void *__restrict__ W,
-                                                     const float *__restrict__ wscale, uint16_t *__restrict__ out,
-                                                     const uint16_t *__restrict__ res, float *__restrict__ part, int M,
-                                                     int N, int K, int epi, int ksteps_per_split, int tiles, int mt,
-                                                     int per_xcd, const uint16_t *__restrict__ gamma = nullptr,
-                                                     float *__restrict__ ssq = nullptr) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t sk_lds[];  // [2][128 W rows + 64 A rows][SK_ROWB]
-  // block b takes tile (b % 8) * per_xcd + b / 8, so each XCD walks its own
-  // contiguous tile range; the mt row blocks of one column tile are
-  // neighbours there and share the W tile through that XCD's L2
-  const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (t >= tiles) return;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n0 = (t / mt) * SW_BN;
-  const int split = blockIdx.y;
-  const int m0 = (t % mt) * SK_BM;
-  const int kbeg = split * ksteps_per_split * 32;
-  const int kend = min(K, kbeg + ksteps_per_split * 32);
-  const int nst = kend > kbeg ? (kend - kbeg + SK_KC - 1) / SK_KC : 0;
-  constexpr uint32_t WES = W8 ? 1u : 2u;  // bytes per W element
-  const buf_rsrc_t ra = make_rsrc(A, (int)min((size_t)M * K * 2, (size_t)0x7FFFFFFF));
-  const buf_rsrc_t rw = make_rsrc(W, (int)min((size_t)N * K * WES, (size_t)0x7FFFFFFF));
-
-  // Staging: thread t moves 16-byte chunk t % 16 of W tile rows t / 16 + 16 j
-  // (j < 8) and A tile rows t / 16 + 16 j (j < 4); each wave instruction
-  // reads 4 rows x 256 contiguous bytes.  Rows outside the operands, k past
-  // the block's range: offsets past the descriptor's range, loaded as zero
-  // without memory traffic.
-  const int ch = tid & 15, r0 = tid >> 4;
-  uint32_t woff[8], aoff[4];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int wr = w_row_of(n0 + r0 + 16 * j, N, epi);
-    woff[j] = wr >= 0 ? ((uint32_t)wr * (uint32_t)K + (uint32_t)(ch * 8)) * WES : 0x80000000u;
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int m = m0 + r0 + 16 * j;
-    aoff[j] = m < M ? ((uint32_t)m * (uint32_t)K + (uint32_t)(ch * 8)) * 2u : 0x80000000u;
-  }
-  u32x4_t wa[8], aa[4], wb[8], ab[4];
-  u32x4_t ga = {0u, 0u, 0u, 0u}, gb = {0u, 0u, 0u, 0u};  // PRENORM: gamma chunk of each stage
-  float ssacc[4] = {0.f, 0.f, 0.f, 0.f};                 // PRENORM: sum of squares of rows r0 + 16 j
-  const buf_rsrc_t rg = make_rsrc(PRENORM ? gamma : A, PRENORM ? K * 2 : 16);
-  auto gload = [&](int s, u32x4_t (&wr)[8], u32x4_t (&ar)[4], u32x4_t &gr) {
-    const int k = kbeg + s * SK_KC + ch * 8;
-    const bool ok = s < nst && k < kend;
-    const uint32_t kb = (uint32_t)(kbeg + s * SK_KC) * 2u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if constexpr (W8) {  // 8 codes in the low half; exact bf16 images when staged
-        const u32x2_t c = buf_ld_u32x2<kAuxNT>(rw, (int)(ok ? woff[j] + kb / 2u : 0x80000000u));
-        wr[j] = u32x4_t{c[0], c[1], 0u, 0u};
-      } else {
-        wr[j] = buf_ld_u32x4<kAuxNT>(rw, (int)(ok ? woff[j] + kb : 0x80000000u));
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ar[j] = buf_ld_u32x4<0>(ra, (int)(ok ? aoff[j] + kb : 0x80000000u));
-    if constexpr (PRENORM) gr = buf_ld_u32x4<0>(rg, (int)(ok ? (uint32_t)(k * 2) : 0x80000000u));
-  };
-  const bool first_col_tile = n0 == 0;
-  auto swrite = [&](int buf, const u32x4_t (&wr)[8], const u32x4_t (&ar)[4], const u32x4_t &gr) {
-    uint8_t *b = sk_lds + buf * (SW_BN + SK_BM) * SK_ROWB;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      u32x4_t wv = wr[j];
-      if constexpr (W8) wv = e4m3x8_to_bf16x8(u32x2_t{wr[j][0], wr[j][1]});
-      *reinterpret_cast<u32x4_t *>(b + (r0 + 16 * j) * SK_ROWB + ch * 16) = wv;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      u32x4_t av = ar[j];
-      if constexpr (PRENORM) {
-        if (first_col_tile) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float lo = bf16_lo(ar[j][e]), hi = bf16_hi(ar[j][e]);
-            ssacc[j] += lo * lo + hi * hi;
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          av[e] = pack_bf16x2(bf16_lo(ar[j][e]) * bf16_lo(gr[e]), bf16_hi(ar[j][e]) * bf16_hi(gr[e]));
-      }
-      *reinterpret_cast<u32x4_t *>(b + (SW_BN + r0 + 16 * j) * SK_ROWB + ch * 16) = av;
-    }
-  };
-  // Each wave runs the whole K range on its 32 columns (two fragments, see
-  // sw_col); the product is formed transposed, D[n][m] = W A^T, so a lane
-  // ends with 4 consecutive columns of one row per fragment.
-  f32x4_t acc[2][4];
-#pragma unroll
-  for (int f = 0; f < 2; ++f)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[f][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const int lr = lane & 15, lg = lane >> 4;
-  auto compute = [&](int buf) {
-    const uint8_t *b = sk_lds + buf * (SW_BN + SK_BM) * SK_ROWB;
-#pragma unroll
-    for (int ks = 0; ks < SK_KC / 32; ++ks) {
-      u32x4_t wf[2], af[4];
-#pragma unroll
-      for (int f = 0; f < 2; ++f)
-        wf[f] = *reinterpret_cast<const u32x4_t *>(b + sw_col(wave, f, lr) * SK_ROWB + (ks * 4 + lg) * 16);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        af[i] = *reinterpret_cast<const u32x4_t *>(b + (SW_BN + i * 16 + lr) * SK_ROWB + (ks * 4 + lg) * 16);
-#pragma unroll
-      for (int f = 0; f < 2; ++f)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[f][i] = mfma16x16x32(wf[f], af[i], acc[f][i]);
-    }
-  };
-  // Two stages in flight in registers, one in LDS: write stage s + 1 while
-  // stage s is consumed, one barrier per stage.
-  gload(0, wa, aa, ga);
-  swrite(0, wa, aa, ga);
-  gload(1, wa, aa, ga);
-  gload(2, wb, ab, gb);
-  __syncthreads();
-  for (int st = 0; st < nst; st += 2) {
-    compute(0);
-    swrite(1, wa, aa, ga);
-    gload(st + 3, wa, aa, ga);
-    __syncthreads();
-    if (st + 1 >= nst) break;
-    compute(1);
-    swrite(0, wb, ab, gb);
-    gload(st + 4, wb, ab, gb);
-    __syncthreads();
-  }
-  if constexpr (PRENORM) {
-    // the 16 lanes of a row (chunks 0..15) hold its partial sums: one per
-    // row and split (stages past nst loaded zeros and added nothing)
-    if (first_col_tile) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float s = group_sum<16>(ssacc[j]);
-        const int m = m0 + r0 + 16 * j;
-        if (ch == 0 && m < M) ssq[(size_t)split * M + m] = s;
-      }
-    }
-  }
-
-  // lane: rows m = m0 + 16 i + lr; fragment f holds logical columns
-  // c_f .. c_f + 3 with c_f = n0 + sw_col(wave, f, 4 lg)
-  const int ncols = logical_cols(N, epi);
-  int cf[2];
-#pragma unroll
-  for (int f = 0; f < 2; ++f) cf[f] = n0 + sw_col(wave, f, 4 * lg);
-  if constexpr (W8) {
-#pragma unroll
-    for (int f = 0; f < 2; ++f)
-      if (cf[f] < ncols) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[f][i] = row_scaled(acc[f][i], wscale, cf[f], N, epi);
-      }
-  }
-  if (part) {  // split-K partial, logical column space
-#pragma unroll
-    for (int f = 0; f < 2; ++f)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + i * 16 + lr;
-        if (m < M && cf[f] < ncols)
-          *reinterpret_cast<f32x4_t *>(part + ((size_t)split * M + m) * ncols + cf[f]) = acc[f][i];
-      }
-    return;
-  }
-  if (epi == EPI_SILU_MUL) {
-    // fragment 0 holds gate sums, fragment 1 their up partners
-    const int F = N >> 1;
-    const int fo = ((n0 + (wave >> 1) * 64) >> 1) + (wave & 1) * 16 + 4 * lg;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + i * 16 + lr;
-      if (m < M && fo < F) {
-        const f32x4_t g = acc[0][i], u = acc[1][i];
-        const u32x2_t w = {pack_bf16x2(silu_f(g[0]) * u[0], silu_f(g[1]) * u[1]),
-                           pack_bf16x2(silu_f(g[2]) * u[2], silu_f(g[3]) * u[3])};
-        *reinterpret_cast<u32x2_t *>(out + (size_t)m * F + fo) = w;
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int f = 0; f < 2; ++f) {
-    const int n = cf[f];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + i * 16 + lr;
-      if (m < M && n < N) {
-        f32x4_t v = acc[f][i];
-        if (epi == EPI_RESIDUAL) {
-          const u32x2_t r = *reinterpret_cast<const u32x2_t *>(res + (size_t)m * N + n);
-          v[0] += bf16_lo(r[0]);
-          v[1] += bf16_hi(r[0]);
-          v[2] += bf16_lo(r[1]);
-          v[3] += bf16_hi(r[1]);
-        }
-        const u32x2_t w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-        *reinterpret_cast<u32x2_t *>(out + (size_t)m * N + n) = w;
-      }
-    }
-  }
-}
 
 // Fragment-packed weights.  A packed copy of W [N][K] (N % 16 == 0,
 // K % 32 == 0) stores each 16-row x 32-column block as one contiguous
@@ -319,13 +141,17 @@ __global__ __launch_bounds__(256) void k_pack_weight(const uint16_t *__restrict_
 }
 
 // The weight-streaming kernel on packed bf16 weights.  Same block, columns,
-// split ranges, products and epilogues as k_gemm_skinny<false>, but each
+// split ranges, products and epilogues as k_gemm_stream<64, false>, but each
 // wave loads its W operands straight into registers from the packed copy
 // (every element of W is used by one wave only, so W needs no LDS), three
 // 128-wide K stages ahead in a ring of three register sets; only A passes
 // through LDS (three buffers).  The products take the same operands in the
-// same order, so the sums are bitwise those of k_gemm_skinny<false>.
+// same order, so the sums are bitwise those of k_gemm_stream<64, false>.
+// It stays for up to 64 rows because its split products are faster (8B down
+// 24.7 against 29.7 us, qkv with the norm 15.6 against 18.2, o the same).
 constexpr int SP_LDS = 3 * SK_BM * SK_ROWB;
+constexpr int SP_LDS_ONE = 96 * 1024;  // as launched: keeps one block per CU
+static_assert(SP_LDS_ONE >= SP_LDS, "LDS");
 template <bool PRENORM = false>
 __global__ __launch_bounds__(256) void k_gemm_skinny_packed(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Wp,
                                                             uint16_t *__restrict__ out, const uint16_t *__restrict__ res,
@@ -361,10 +187,13 @@ __global__ __launch_bounds__(256) void k_gemm_skinny_packed(const uint16_t *__re
   }
   const int kc0 = kbeg >> 5, kc_end = kend >> 5;
   u32x4_t w0[2][4], w1[2][4], w2[2][4];
+  // stage s of the walk is K stage at(s) of the range (see k_start)
+  const int rot = gridDim.y == 1 ? k_start(t / mt, tiles / mt, nst) : 0;
+  auto at = [&](int s) { return s + rot < nst ? s + rot : s + rot - nst; };
   auto wload = [&](int s, u32x4_t (&wr)[2][4]) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      const int kc = kc0 + s * 4 + ks;
+      const int kc = kc0 + at(s) * 4 + ks;
 #pragma unroll
       for (int f = 0; f < 2; ++f)
         wr[f][ks] = buf_ld_u32x4<kAuxNT>(
@@ -385,9 +214,9 @@ __global__ __launch_bounds__(256) void k_gemm_skinny_packed(const uint16_t *__re
   float ssacc[4] = {0.f, 0.f, 0.f, 0.f};
   const buf_rsrc_t rg = make_rsrc(PRENORM ? gamma : A, PRENORM ? K * 2 : 16);
   auto aload = [&](int s) {
-    const int k = kbeg + s * SK_KC + ch * 8;
+    const int k = kbeg + at(s) * SK_KC + ch * 8;
     const bool ok = s < nst && k < kend;
-    const uint32_t kb = (uint32_t)(kbeg + s * SK_KC) * 2u;
+    const uint32_t kb = (uint32_t)(kbeg + at(s) * SK_KC) * 2u;
 #pragma unroll
     for (int j = 0; j < 4; ++j) aa[j] = buf_ld_u32x4<0>(ra, (int)(ok ? aoff[j] + kb : 0x80000000u));
     if constexpr (PRENORM) ga = buf_ld_u32x4<0>(rg, (int)(ok ? (uint32_t)(k * 2) : 0x80000000u));
@@ -576,6 +405,293 @@ __global__ __launch_bounds__(256) void k_gemm_splitk_epilogue(const float *__res
 }
 
 // ===========================================================================
+// stream: the weight-streaming kernel.  What bounds it is W's way from HBM,
+// so all of the CU's LDS is a ring of K stages loaded straight into it (no
+// register between, nothing for the compiler to wait on), and each stage waits
+// for its own loads by count, leaving 4 or 5 stages (96-120 KiB per CU at up
+// to 64 rows) in flight across the one barrier a stage has.  The kernel before
+// it staged through registers, two 128-wide stages ahead, and drained at each
+// barrier: 64 rows, qkv 22.3 -> 17.8 us, gate/up 51.2 -> 43.3; 8-bit W at 37
+// rows, gate/up 41.0 -> 28.1, down 24.7 -> 20.4; more rows: stream_bm.
+//
+// Wave grid: 1 x 4 (32 columns a wave, all rows) to 64 rows, 2 x 2 (64
+// columns, half the rows) above, which halves the LDS reads per product.
+// PRENORM (split-K partials only): A holds the rows x of an RMSNorm that
+// precedes the product.  A landed stage's rows become bf16(x * gamma) in place
+// one stage before they are multiplied, and the blocks of the first column
+// tile write each row's partial sum of squares over their K range to
+// ssq[split][M]; the row scale 1 / sqrt(mean(x^2) + eps) is applied to the
+// summed partials by the consumer (RMSNorm(x) g W^T = inv * ((x g) W^T)).
+// ===========================================================================
+constexpr int ST_BN = 128;  // logical columns per block
+// Rows per block, K per stage and ring depth: a stage holds 128 W rows and BM
+// A rows of KC values (bf16: 64, rows of 128 bytes; 8-bit W: 128, W rows of
+// 128 bytes of codes), the ring fills the CU's LDS (160 KiB less the norm
+// gains), all but one stage of it in flight.
+template <int BM, bool W8, bool PRENORM>
+struct StreamTraits {
+  static constexpr int KC = W8 ? 128 : 64;
+  static constexpr int WROW = KC * (W8 ? 1 : 2);       // bytes of a W row
+  static constexpr int AROW = KC * 2;                 // bytes of an A row
+  static constexpr int W_BYTES = ST_BN * WROW;        // W part of a stage
+  static constexpr int A_BYTES = BM * AROW;
+  static constexpr int G_BYTES = PRENORM ? 256 : 0;   // the stage's norm gains
+  static constexpr int STAGE = W_BYTES + A_BYTES + G_BYTES;
+  static constexpr int R = (160 * 1024) / STAGE;
+  static constexpr int LDS = R * STAGE;
+  static_assert(R >= 2, "ring depth");
+  static constexpr int WM = BM >= 128 ? 2 : 1, WN = 4 / WM;  // wave grid
+  static constexpr int NF = ST_BN / WN / 16;          // 16-column fragments per wave
+  static constexpr int NI = BM / WM / 16;             // 16-row blocks per wave
+  static constexpr int LA = A_BYTES / 4096, LW = W_BYTES / 4096;  // load instructions per wave and stage
+};
+
+template <int BM, bool W8, bool PRENORM>
+__global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict__ A, const void *__restrict__ W,
+                                                     const float *__restrict__ wscale, uint16_t *__restrict__ out,
+                                                     const uint16_t *__restrict__ res, float *__restrict__ part, int M,
+                                                     int N, int K, int epi, int ksteps_per_split, int tiles, int mt,
+                                                     int per_xcd, const uint16_t *__restrict__ gamma,
+                                                     float *__restrict__ ssq) {
+  using Tr = StreamTraits<BM, W8, PRENORM>;
+  constexpr int KC = Tr::KC, R = Tr::R, NF = Tr::NF, NI = Tr::NI, LA = Tr::LA, LW = Tr::LW, AROW = Tr::AROW;
+  constexpr int NL = LA + LW + (PRENORM ? 1 : 0);  // loads per wave and stage
+  constexpr uint32_t WES = W8 ? 1u : 2u;
+  extern __shared__ __attribute__((aligned(16))) uint8_t st_lds[];  // [R][W | A | gains]
+  // block b takes tile (b % 8) * per_xcd + b / 8, so each XCD walks its own
+  // contiguous tile range; the mt row blocks of one column tile are
+  // neighbours there and share the W tile through that XCD's L2
+  const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (t >= tiles) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = Tr::WM == 2 ? wave >> 1 : 0, wn = Tr::WM == 2 ? wave & 1 : wave;
+  const int n0 = (t / mt) * ST_BN, m0 = (t % mt) * BM;
+  const int split = blockIdx.y;
+  const int kbeg = split * ksteps_per_split * 32;
+  const int kend = min(K, kbeg + ksteps_per_split * 32);
+  const int nst = kend > kbeg ? (kend - kbeg + KC - 1) / KC : 0;
+  const uint32_t a_bytes = (uint32_t)min((size_t)M * K * 2, (size_t)0x7FFFFFFF);
+  const uint32_t w_bytes = (uint32_t)min((size_t)N * K * WES, (size_t)0x7FFFFFFF);
+
+  // Loads.  A wave's load instruction i fills 1 KiB of LDS: rows of 128 bytes
+  // (8 of them) or 256 (4); lane l writes 16-byte position l % 8 (l % 16) of
+  // its row with the logical chunk swizzled there.  Rows outside the
+  // operands and k past the block's range point past every descriptor's
+  // range: they load zeros without traffic.
+  auto swz = [](int row, int c, int rowb) { return rowb == 128 ? c ^ ((row >> 1) & 7) : c ^ (row & 15); };
+  constexpr int RPI = 1024 / AROW, CPR = AROW / 16;  // A rows per load instruction, chunks per row
+  constexpr int CK = W8 ? 16 : 8;                    // W values per chunk
+  constexpr int WROW = Tr::WROW, WRPI = 1024 / WROW, WCPR = WROW / 16;
+  uint32_t woff[LW], aoff[LA];
+  auto wchunk = [&](int i) { return swz((wave * LW + i) * WRPI + lane / WCPR, lane % WCPR, WROW); };
+  auto achunk = [&](int i) { return swz((wave * LA + i) * RPI + lane / CPR, lane % CPR, AROW); };
+#pragma unroll
+  for (int i = 0; i < LW; ++i) {
+    const int wr = w_row_of(n0 + (wave * LW + i) * WRPI + lane / WCPR, N, epi);
+    woff[i] = wr >= 0 ? (uint32_t)wr * (uint32_t)K * WES + (uint32_t)wchunk(i) * 16u : 0x80000000u;
+  }
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int m = m0 + (wave * LA + i) * RPI + lane / CPR;
+    aoff[i] = m < M ? (uint32_t)m * (uint32_t)K * 2u + (uint32_t)achunk(i) * 16u : 0x80000000u;
+  }
+  const u32x4_t ra = raw_rsrc(A, a_bytes), rw = raw_rsrc(W, w_bytes);
+  const u32x4_t rg = raw_rsrc(PRENORM ? gamma : A, PRENORM ? (uint32_t)K * 2u : 0u);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)st_lds;
+  // stage s into the ring slot at byte `slot`
+  const int rot = gridDim.y == 1 ? k_start(t / mt, tiles / mt, (kend - kbeg + 127) / 128) * (128 / KC) : 0;
+  auto issue = [&](int s, uint32_t slot) {
+    const int k0 = s >= nst ? kend : kbeg + (s + rot < nst ? s + rot : s + rot - nst) * KC;
+    const uint32_t dw = lds0 + slot + (uint32_t)(wave * LW) * 1024u;
+    const uint32_t da = lds0 + slot + Tr::W_BYTES + (uint32_t)(wave * LA) * 1024u;
+    if constexpr (PRENORM) {  // (the four waves write the same values)
+      const uint32_t go = (uint32_t)(k0 * 2 + lane * 4);
+      dma_lds4(rg, k0 < kend ? go : 0x80000000u, 0u, lds0 + slot + Tr::W_BYTES + Tr::A_BYTES);
+    }
+    if (k0 + KC <= kend) {
+#pragma unroll
+      for (int i = 0; i < LA; ++i) dma_lds16(ra, aoff[i], (uint32_t)k0 * 2u, da + i * 1024);
+#pragma unroll
+      for (int i = 0; i < LW; ++i) dma_lds16(rw, woff[i], (uint32_t)k0 * WES, dw + i * 1024);
+    } else {  // the last stage of a ragged range, or past it
+#pragma unroll
+      for (int i = 0; i < LA; ++i)
+        dma_lds16(ra, k0 + achunk(i) * 8 < kend && aoff[i] != 0x80000000u ? aoff[i] + (uint32_t)k0 * 2u : 0x80000000u, 0u,
+                  da + i * 1024);
+#pragma unroll
+      for (int i = 0; i < LW; ++i)
+        dma_lds16(rw, k0 + wchunk(i) * CK < kend && woff[i] != 0x80000000u ? woff[i] + (uint32_t)k0 * WES : 0x80000000u,
+                  0u, dw + i * 1024);
+    }
+  };
+
+  f32x4_t acc[NF][NI];
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int i = 0; i < NI; ++i) acc[f][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int lr = lane & 15, lg = lane >> 4;
+  // block-local logical column of fragment f's first W row
+  auto fcol = [&](int f) { return NF == 2 ? sw_col(wn, f, 0) : wn * 64 + f * 16; };
+  const int sw8 = (lr >> 1) & 7;
+  auto compute = [&](uint32_t slot) {
+    const uint8_t *w = st_lds + slot + lr * WROW;
+    const uint8_t *a = st_lds + slot + Tr::W_BYTES + (wm * NI * 16 + lr) * AROW;
+#pragma unroll
+    for (int q = 0; q < KC / (W8 ? 64 : 32); ++q) {
+      u32x4_t wc[NF];
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        wc[f] = *reinterpret_cast<const u32x4_t *>(w + fcol(f) * WROW + (((q * 4 + lg) ^ (WROW == 128 ? sw8 : lr)) << 4));
+#pragma unroll
+      for (int h = 0; h < (W8 ? 2 : 1); ++h) {
+        // 8-bit W: a lane's 16 codes are k = 16 (4 q + lg) .. + 15, A's chunks in the same order
+        const int c = W8 ? (2 * (q * 4 + lg) + h) ^ lr : (q * 4 + lg) ^ (AROW == 128 ? sw8 : lr);
+        u32x4_t wf[NF], af[NI];
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+          wf[f] = W8 ? e4m3x8_to_bf16x8(u32x2_t{wc[f][2 * h], wc[f][2 * h + 1]}) : wc[f];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) af[i] = *reinterpret_cast<const u32x4_t *>(a + i * 16 * AROW + (c << 4));
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+          for (int i = 0; i < NI; ++i) acc[f][i] = mfma16x16x32(wf[f], af[i], acc[f][i]);
+      }
+    }
+  };
+  // PRENORM: the A rows of a landed stage become bf16(x * gain) in place, the
+  // blocks of the first column tile adding up their squares on the way
+  constexpr int TJ = Tr::A_BYTES / 4096;
+  float ssacc[TJ];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) ssacc[j] = 0.f;
+  const bool first_col_tile = n0 == 0;
+  auto prenorm = [&](uint32_t slot) {
+    const int p = tid % CPR, row = tid / CPR;  // rows + (256 / CPR) j: the same chunk for all j
+    const int c = swz(row, p, AROW);
+    uint8_t *a = st_lds + slot + Tr::W_BYTES + row * AROW + p * 16;
+    const u32x4_t g = *reinterpret_cast<const u32x4_t *>(st_lds + slot + Tr::W_BYTES + Tr::A_BYTES + c * 16);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      u32x4_t x = *reinterpret_cast<const u32x4_t *>(a + j * 4096);
+      if (first_col_tile) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float lo = bf16_lo(x[e]), hi = bf16_hi(x[e]);
+          ssacc[j] += lo * lo + hi * hi;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = pack_bf16x2(bf16_lo(x[e]) * bf16_lo(g[e]), bf16_hi(x[e]) * bf16_hi(g[e]));
+      *reinterpret_cast<u32x4_t *>(a + j * 4096) = x;
+    }
+  };
+
+  // Stage s: wait until it (PRENORM: and the A rows of stage s + 1) landed in
+  // every wave, refill the slot read in stage s - 1 with stage s + R - 1, then
+  // multiply.  The younger stages stay in flight across the barrier.
+  auto next = [&](uint32_t slot) { return slot + Tr::STAGE == Tr::LDS ? 0u : slot + Tr::STAGE; };
+  uint32_t fill = 0;
+#pragma unroll
+  for (int s = 0; s < R - 1; ++s) {
+    issue(s, fill);
+    fill += Tr::STAGE;
+  }
+  uint32_t slot = 0;
+  if constexpr (PRENORM) {
+    wait_loads<(R - 2) * NL + LW>();
+    wave_barrier();
+    prenorm(0);
+  }
+  for (int s = 0; s < nst; ++s) {
+    wait_loads<PRENORM ? (R - 3) * NL + LW : (R - 2) * NL>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wave_barrier();
+    issue(s + R - 1, fill);
+    fill = next(fill);
+    if constexpr (PRENORM) prenorm(next(slot));
+    compute(slot);
+    slot = next(slot);
+  }
+  wait_loads<0>();
+  if constexpr (PRENORM) {
+    if (first_col_tile) {
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        const float v = group_sum<CPR>(ssacc[j]);
+        const int m = m0 + tid / CPR + (256 / CPR) * j;
+        if (tid % CPR == 0 && m < M) ssq[(size_t)split * M + m] = v;
+      }
+    }
+  }
+
+  // lane: rows m = m0 + 16 (wm NI + i) + lr; fragment f holds logical columns
+  // n0 + fcol(f) + 4 lg .. + 3
+  const int ncols = logical_cols(N, epi);
+  if constexpr (W8) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const int c = n0 + fcol(f) + 4 * lg;
+      if (c < ncols) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) acc[f][i] = row_scaled(acc[f][i], wscale, c, N, epi);
+      }
+    }
+  }
+  const int mrow = m0 + wm * NI * 16 + lr;
+  if (part) {  // split-K partial, logical column space
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int m = mrow + i * 16, c = n0 + fcol(f) + 4 * lg;
+        if (m < M && c < ncols) *reinterpret_cast<f32x4_t *>(part + ((size_t)split * M + m) * ncols + c) = acc[f][i];
+      }
+    return;
+  }
+  if (epi == EPI_SILU_MUL) {
+    // fragment f holds gate sums, fragment f + NF / 2 their up partners
+    const int F = N >> 1;
+#pragma unroll
+    for (int f = 0; f < NF / 2; ++f) {
+      const int c = n0 + fcol(f);  // (32 gate columns, then 32 up, per group of 64)
+      const int fo = (c >> 6) * 32 + (c & 31) + 4 * lg;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int m = mrow + i * 16;
+        if (m < M && fo < F) {
+          const f32x4_t g = acc[f][i], u = acc[f + NF / 2][i];
+          *reinterpret_cast<u32x2_t *>(out + (size_t)m * F + fo) =
+              u32x2_t{pack_bf16x2(silu_f(g[0]) * u[0], silu_f(g[1]) * u[1]),
+                      pack_bf16x2(silu_f(g[2]) * u[2], silu_f(g[3]) * u[3])};
+        }
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const int n = n0 + fcol(f) + 4 * lg;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int m = mrow + i * 16;
+      if (m < M && n < N) {
+        f32x4_t v = acc[f][i];
+        if (epi == EPI_RESIDUAL) {
+          const u32x2_t r = *reinterpret_cast<const u32x2_t *>(res + (size_t)m * N + n);
+          v += f32x4_t{bf16_lo(r[0]), bf16_hi(r[0]), bf16_lo(r[1]), bf16_hi(r[1])};
+        }
+        *reinterpret_cast<u32x2_t *>(out + (size_t)m * N + n) =
+            u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      }
+    }
+  }
+}
+
+// ===========================================================================
 // tiled
 // ===========================================================================
 constexpr int TL_BM = 128, TL_BN = 128, TL_BK = 64, TL_LDK = TL_BK + 8;
@@ -752,31 +868,6 @@ struct GroupedArgs {
   int max_tiles, a_nrows, f32_out;
 };
 
-// One 16-byte-per-lane buffer load straight into LDS at byte address lds +
-// 16 lane (lds wave-uniform).  In assembly, so that the compiler does not
-// take every later LDS read to depend on it and drain all loads in flight:
-// the kernel counts its own loads (s_waitcnt vmcnt) instead.  The load
-// writes no register.
-__device__ __forceinline__ void bg_dma16(u32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void bg_wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void bg_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-__device__ __forceinline__ u32x4_t bg_rsrc(const void *base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  return u32x4_t{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, bytes, 0x00020000u};
-}
-
 template <int epi, bool W8, bool GROUPED>
 __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restrict__ A, const void *__restrict__ W,
                                                          const float *__restrict__ wscale, uint16_t *__restrict__ out,
@@ -859,19 +950,19 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
   // half h of K tile kt into the buffer at dst_buf (past the last K tile: an
   // empty range, no traffic)
   auto dma_a = [&](int kt, int h, uint32_t dst_buf) {
-    const u32x4_t r = bg_rsrc(A, kt < kt1 ? a_bytes : 0u);
+    const u32x4_t r = raw_rsrc(A, kt < kt1 ? a_bytes : 0u);
     const uint32_t kb = kt < kt1 ? (uint32_t)kt * (BG_BK * 2u) : 0u;
     const uint32_t dst = lds0 + dst_buf + (uint32_t)(h * BG_HALF_BYTES + wave * 2048);
-    bg_dma16(r, aoff[h][0], kb, dst);
-    bg_dma16(r, aoff[h][1], kb, dst + 1024);
+    dma_lds16(r, aoff[h][0], kb, dst);
+    dma_lds16(r, aoff[h][1], kb, dst + 1024);
   };
   auto dma_w = [&](int kt, int h, uint32_t dst_buf) {
-    const u32x4_t r = bg_rsrc(Wt, kt < kt1 ? w_bytes : 0u);
+    const u32x4_t r = raw_rsrc(Wt, kt < kt1 ? w_bytes : 0u);
     const uint32_t kb = kt < kt1 ? (uint32_t)kt * (BG_BK * WES) : 0u;
     const uint32_t dst =
         lds0 + dst_buf + (uint32_t)(BG_TILE_BYTES + h * BG_HALF_BYTES + wave * (W8 ? 1024 : 2048));
-    bg_dma16(r, woff[h][0], kb, dst);
-    if constexpr (!W8) bg_dma16(r, woff[h][1], kb, dst + 1024);
+    dma_lds16(r, woff[h][0], kb, dst);
+    if constexpr (!W8) dma_lds16(r, woff[h][1], kb, dst + 1024);
   };
 
   f32x4_t acc[4][8];  // [W block jn][A block im]: rows n, cols m
@@ -924,7 +1015,7 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           acc[hw * 2 + j][ha * 4 + i] = mfma16x16x32(wf[j][ks], af[i][ks], acc[hw * 2 + j][ha * 4 + i]);
-    bg_barrier();
+    wave_barrier();
   };
   constexpr int NW_ = W8 ? 1 : 2;  // load instructions of a W half (an A half has 2)
   constexpr uint32_t BUF = 2 * BG_TILE_BYTES;
@@ -936,40 +1027,40 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
   dma_a(kt0 + 1, 0, BUF);
   dma_w(kt0 + 1, 0, BUF);
   dma_w(kt0 + 1, 1, BUF);
-  bg_wait_loads<4 + 3 * NW_>();
-  bg_barrier();
+  wait_loads<4 + 3 * NW_>();
+  wave_barrier();
   read_a(abase, 0, ax);
-  if (wm == 1) bg_barrier();
+  if (wm == 1) wave_barrier();
   for (int kt = kt0; kt < kt1; ++kt) {
     read_w(wbase, 0, w0);
     dma_a(kt + 1, 1, buf ^ BUF);
-    bg_wait_loads<6 + 2 * NW_>();
-    bg_barrier();
+    wait_loads<6 + 2 * NW_>();
+    wave_barrier();
     products(w0, ax, 0, 0);
 
     read_w(wbase, 1, w1);
     dma_a(kt + 2, 0, buf);
-    bg_wait_loads<6 + 2 * NW_>();
-    bg_barrier();
+    wait_loads<6 + 2 * NW_>();
+    wave_barrier();
     products(w1, ax, 1, 0);
 
     read_a(abase, 1, ay);
     dma_w(kt + 2, 0, buf);
-    bg_wait_loads<4 + 3 * NW_>();
-    bg_barrier();
+    wait_loads<4 + 3 * NW_>();
+    wave_barrier();
     products(w1, ay, 1, 1);
 
     abase ^= BUF;
     wbase ^= BUF;
     read_a(abase, 0, ax);
     dma_w(kt + 2, 1, buf);
-    bg_wait_loads<4 + 3 * NW_>();
-    bg_barrier();
+    wait_loads<4 + 3 * NW_>();
+    wave_barrier();
     products(w0, ay, 0, 1);
     buf ^= BUF;
   }
-  bg_wait_loads<0>();
-  if (wm == 0) bg_barrier();
+  wait_loads<0>();
+  if (wm == 0) wave_barrier();
 
   // Epilogue: lane holds out[m][n .. n + 3] with m = m0 + wm 128 + 16 im + lr,
   // n = n0 + wn 64 + 16 jn + 4 lg (N and F are multiples of 4, so a group of
@@ -1194,9 +1285,8 @@ __global__ __launch_bounds__(256) void k_gemm_grouped(const uint16_t *__restrict
 // ===========================================================================
 // planning and launch
 // ===========================================================================
-// Row counts up to this use the skinny kernel (weight streaming: the row
-// blocks of a column tile run side by side and read W once from HBM).
-constexpr int kSkinnyMaxRows = 256;
+// Row counts up to this use the weight-streaming kernels.
+constexpr int kStreamMaxRows = 256;
 
 // The split-K sum of a residual GEMM and the RMSNorm of its rows in one
 // pass: h = bf16(sum_s part[s] + res) is stored (the splits summed in order,
@@ -1307,8 +1397,21 @@ static hipError_t finish_splitk(const float *part, int splits, uint16_t *out, co
   return launch_splitk_epilogue(part, splits, out, res, M, N, epi, st);
 }
 
-static int skinny_splits(int M, int N, int K) {
-  const int tiles = ((N + SW_BN - 1) / SW_BN) * ((M + SK_BM - 1) / SK_BM);
+// Rows per block of the stream kernel: all of the batch, so that W goes to a
+// CU once (160 rows: gate/up 109 -> 62 us, o 32 -> 22, down 64 -> 39 against
+// three blocks of 64 rows); 8-bit W stops at 128 rows, where its ring is three
+// stages deep.  A W that fits one XCD's L2 (4 MiB) costs nothing to read
+// again, and then more, smaller blocks have the shorter chain (the tiny
+// layer's four products: 47 us at 192 rows per block against 34 at 64).
+static int stream_bm(int M, int N, int K, bool w8) {
+  if (M <= 64 || (size_t)N * K * (w8 ? 1 : 2) <= ((size_t)4 << 20)) return 64;
+  if (M <= 128 || w8) return 128;
+  return M <= 192 ? 192 : 256;
+}
+
+static int stream_splits(int M, int N, int K, bool w8) {
+  const int bm = stream_bm(M, N, K, w8);
+  const int tiles = ((N + ST_BN - 1) / ST_BN) * ((M + bm - 1) / bm);
   const int nsteps = (K + 31) / 32;
   // one block per CU (256 CUs).  A grid that covers at least 3/4 of the CUs
   // is not split; otherwise K is split into the count whose rounds of 256
@@ -1324,6 +1427,21 @@ static int skinny_splits(int M, int N, int K) {
   return best;
 }
 
+// 129 to 255 rows: both kernels read W once.  The 256 x 256 tiles (padded to
+// 256 rows) are the faster ones where they fill 3/4 of the CUs unsplit (70B
+// gate/up at 200 rows: 205 us against 267), where both kernels split a long K
+// over many columns (70B down 127 against 143, qkv 57 against 63, o 52 both),
+// and for 8-bit W, which the stream kernel would read twice (8B gate/up 63
+// against 78, qkv 33 against 43, down 47 against 45; 70B 194 against 277).  The stream
+// kernel is where its 128 columns a block need no split and 256 would (8B
+// gate/up at 160 / 240 rows: 58 / 71 against 75 / 83), and on the narrower
+// split products (8B down at 200 rows 44 against 53, qkv 28 against 33).
+static bool big_below_256(int M, int ncols, int K, bool w8) {
+  if (M <= 128 || M >= 256) return false;
+  if (w8 || (ncols + BG_BN - 1) / BG_BN >= 192) return true;
+  return (ncols + ST_BN - 1) / ST_BN < 192 && ncols >= 8192 && K >= 8192;
+}
+
 GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8) {
   GemmPlan p{};
   p.splits = 1;
@@ -1336,7 +1454,7 @@ GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8) {
                     (size_t)BG_BM * ncols * 4 < ((size_t)1 << 31);
   // 256 x 256 tiles once the grid covers at least half the CUs
   const long big_tiles = (long)((M + BG_BM - 1) / BG_BM) * ((ncols + BG_BN - 1) / BG_BN);
-  if (K % BG_BK == 0 && N % 8 == 0 && fits && M >= 256) {
+  if (K % BG_BK == 0 && N % 8 == 0 && fits && (M >= 256 || big_below_256(M, ncols, K, w8))) {
     // one block per CU: split K while the tiles cover at most half the CUs,
     // keeping at least 8 K tiles per split
     p.kind = 2;
@@ -1352,11 +1470,11 @@ GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8) {
     p.ws_bytes = p.splits > 1 ? (size_t)p.splits * M * ncols * sizeof(float) : 0;
     return p;
   }
-  // the skinny kernel addresses both operands through 32-bit buffer ranges
+  // the weight-streaming kernels address both operands through 32-bit buffer ranges
   const bool sk_fits = (size_t)N * K * (w8 ? 1 : 2) < ((size_t)1 << 31) && (size_t)M * K * 2 < ((size_t)1 << 31);
-  if ((M <= kSkinnyMaxRows || w8) && sk_fits) {  // (the tiled kernel reads bf16 weights only)
+  if ((M <= kStreamMaxRows || w8) && sk_fits) {  // (the tiled kernel reads bf16 weights only)
     p.kind = 0;
-    p.splits = skinny_splits(M, ncols, K);
+    p.splits = stream_splits(M, ncols, K, w8);
     p.ws_bytes = p.splits > 1 ? (size_t)p.splits * M * ncols * sizeof(float) : 0;
     return p;
   }
@@ -1395,6 +1513,40 @@ static void launch_big(dim3 grid, hipStream_t st, const uint16_t *A, const void 
                      per_xcd, kt_per, ga);
 }
 
+template <bool PRENORM>
+static hipError_t launch_stream(const uint16_t *A, const void *W, const float *wscale, uint16_t *out,
+                                const uint16_t *res, float *part, int M, int N, int K, int epi, int splits,
+                                hipStream_t st, const uint16_t *gamma, float *ssq) {
+  const bool w8 = wscale != nullptr;
+  const int bm = stream_bm(M, N, K, w8);
+  const int ncols = logical_cols(N, epi);
+  const int nsteps = (K + 31) / 32;
+  const int per = (nsteps + splits - 1) / splits;
+  const int mt = (M + bm - 1) / bm;
+  const int tiles = ((ncols + ST_BN - 1) / ST_BN) * mt;
+  const int per_xcd = (tiles + 7) / 8;
+  const dim3 grid(8 * per_xcd, splits);
+#define EB_STREAM(BM_, W8_)                                                                                         \
+  hipLaunchKernelGGL((k_gemm_stream<BM_, W8_, PRENORM>), grid, dim3(256), (StreamTraits<BM_, W8_, PRENORM>::LDS), st, A, \
+                     W, wscale, out, res, part, M, N, K, epi, per, tiles, mt, per_xcd, gamma, ssq)
+  if (w8) {
+    if (bm == 64)
+      EB_STREAM(64, true);
+    else
+      EB_STREAM(128, true);
+  } else if (bm == 64) {
+    EB_STREAM(64, false);
+  } else if (bm == 128) {
+    EB_STREAM(128, false);
+  } else if (bm == 192) {
+    EB_STREAM(192, false);
+  } else {
+    EB_STREAM(256, false);
+  }
+#undef EB_STREAM
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm(const GemmPlan &p, const uint16_t *A, const void *W, const float *wscale, uint16_t *out,
                        const uint16_t *res, int M, int N, int K, int epi, void *ws, hipStream_t st, NormFuse *nf,
                        const uint16_t *Wp) {
@@ -1412,15 +1564,14 @@ hipError_t launch_gemm(const GemmPlan &p, const uint16_t *A, const void *W, cons
     const int tiles = ((ncols + SW_BN - 1) / SW_BN) * mt;
     const int per_xcd = (tiles + 7) / 8;
     dim3 grid(8 * per_xcd, splits);
-    if (w8)
-      hipLaunchKernelGGL(k_gemm_skinny<true>, grid, dim3(256), SW_LDS, st, A, W, wscale, out, res, part, M, N, K, epi,
-                         per, tiles, mt, per_xcd);
-    else if (Wp && packed_ok(N, K, epi))  // (SW_LDS of LDS keeps one block per CU)
-      hipLaunchKernelGGL(k_gemm_skinny_packed<false>, grid, dim3(256), SW_LDS, st, A, Wp, out, res, part, M, N, K,
-                         epi, per, tiles, mt, per_xcd);
-    else
-      hipLaunchKernelGGL(k_gemm_skinny<false>, grid, dim3(256), SW_LDS, st, A, W, wscale, out, res, part, M, N, K,
-                         epi, per, tiles, mt, per_xcd);
+    if (!(Wp && packed_ok(N, K, epi) && M <= kPackedMaxRows)) {
+      const hipError_t e =
+          launch_stream<false>(A, W, wscale, out, res, part, M, N, K, epi, splits, st, nullptr, nullptr);
+      if (e != hipSuccess || splits == 1) return e;
+      return finish_splitk(part, splits, out, res, M, N, epi, nf, st);
+    }
+    hipLaunchKernelGGL(k_gemm_skinny_packed<false>, grid, dim3(256), SP_LDS_ONE, st, A, Wp, out, res, part, M, N, K, epi,
+                       per, tiles, mt, per_xcd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     return finish_splitk(part, splits, out, res, M, N, epi, nf, st);
@@ -1465,21 +1616,15 @@ hipError_t launch_gemm_prenorm(const GemmPlan &p, const uint16_t *x, const uint1
                                const uint16_t *Wp) {
   if (M <= 0) return hipSuccess;
   if (p.kind != 0 || p.splits < 2) return hipErrorInvalidValue;
+  if (!(Wp && packed_ok(N, K, EPI_STORE) && M <= kPackedMaxRows))
+    return launch_stream<true>(x, W, wscale, nullptr, nullptr, part, M, N, K, (int)EPI_STORE, p.splits, st, gamma, ssq);
   const int nsteps = (K + 31) / 32;
   const int per = (nsteps + p.splits - 1) / p.splits;
   const int mt = (M + SK_BM - 1) / SK_BM;
   const int tiles = ((N + SW_BN - 1) / SW_BN) * mt;
   const int per_xcd = (tiles + 7) / 8;
-  dim3 grid(8 * per_xcd, p.splits);
-  if (wscale)
-    hipLaunchKernelGGL((k_gemm_skinny<true, true>), grid, dim3(256), SW_LDS, st, x, W, wscale, nullptr, nullptr, part,
-                       M, N, K, (int)EPI_STORE, per, tiles, mt, per_xcd, gamma, ssq);
-  else if (Wp && packed_ok(N, K, EPI_STORE))
-    hipLaunchKernelGGL((k_gemm_skinny_packed<true>), grid, dim3(256), SW_LDS, st, x, Wp, nullptr, nullptr, part, M, N,
-                       K, (int)EPI_STORE, per, tiles, mt, per_xcd, gamma, ssq);
-  else
-    hipLaunchKernelGGL((k_gemm_skinny<false, true>), grid, dim3(256), SW_LDS, st, x, W, wscale, nullptr, nullptr,
-                       part, M, N, K, (int)EPI_STORE, per, tiles, mt, per_xcd, gamma, ssq);
+  hipLaunchKernelGGL((k_gemm_skinny_packed<true>), dim3(8 * per_xcd, p.splits), dim3(256), SP_LDS_ONE, st, x, Wp, nullptr,
+                     nullptr, part, M, N, K, (int)EPI_STORE, per, tiles, mt, per_xcd, gamma, ssq);
   return hipGetLastError();
 }
 

@@ -1,0 +1,92 @@
+"""GEMM kernels at the edges of their tiles: row counts around the rows per
+block of the weight-streaming kernel, W on both sides of the size that
+decides them, K ranges that end inside a stage (for 8-bit W inside a 16-code
+chunk), and the tiles of the 256 x 256 kernel.
+
+The bound per element: the result is one bf16 rounding (half an ulp, 2^-9
+relative) of a sum whose fp32 additions each round by at most 2^-24 of the
+partial sums, themselves at most S = |A| |W|^T; K additions in any order stay
+within K 2^-24 S (taken twice, and the bf16 part twice)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_00516_amd import binding as B
+from paper_2606_00516_amd import inputs as gen
+from tests._cases import make_case
+from tests._gpu import DevCase, maxrel, to_f32
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(M, N, K, epi, w8, seed=0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed + M + N + K)
+    A = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    R = torch.randn(M, N, generator=g, device="cuda").to(torch.bfloat16)
+    if w8:
+        W, s = gen.make_fp8_matrix(N, K, seed + 1, device="cuda", proj_std=0.05)
+        w64 = W.view(torch.float8_e4m3fn).float().double() * s.double()[:, None]
+        got = B.eb_op_gemm_w8(A, W, s, epi, residual=R if epi == "residual" else None)
+    else:
+        W = (torch.randn(N, K, generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+        w64 = W.double()
+        got = B.eb_op_gemm(A, W, epi, residual=R if epi == "residual" else None)
+    p = A.double() @ w64.t()
+    acc = 2 * K * 2.0 ** -24 * (A.double().abs() @ w64.abs().t())
+    if epi == "silu_mul":
+        F = N // 2
+        gate, up = p[:, :F], p[:, F:]
+        ref = gate * torch.sigmoid(gate) * up
+        # |d silu / dx| <= 1.1; the exponential and reciprocal add a few ulps of fp32
+        acc = 1.1 * acc[:, :F] * up.abs() + acc[:, F:] * gate.abs() + 2.0 ** -20 * ref.abs()
+    else:
+        ref = p + (R.double() if epi == "residual" else 0)
+    err = (got.double() - ref).abs()
+    worst = (err - (2.0 ** -8 * ref.abs() + acc + 1e-30)).max().item()
+    assert worst <= 0, (worst, err.max().item())
+
+
+# 4104 x 1032: W of 8.5 MB (rows per block follow the batch; K ends 8 values into a stage and, for codes, into a
+# chunk); 264 x 520: W inside one L2 (blocks of 64 rows)
+@pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
+@pytest.mark.parametrize("N,K", [(4104, 1032), (8208, 1048), (264, 520)])
+@pytest.mark.parametrize("M", [1, 15, 64, 65, 128, 129, 192, 193, 255])
+def test_stream_rows(M, N, K, w8):
+    _check(M, N, K, "store" if M % 2 else "residual", w8)
+
+
+@pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
+@pytest.mark.parametrize("M,N,K", [(33, 28688, 512), (100, 28688, 512), (180, 28688, 264), (240, 28688, 1152),
+                                   (64, 25600, 136), (130, 1376, 256)])
+def test_stream_silu(M, N, K, w8):
+    """Unsplit gate/up products (each column tile starts its K walk elsewhere)."""
+    _check(M, N, K, "silu_mul", w8)
+
+
+@pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
+@pytest.mark.parametrize("epi", ["store", "residual", "silu_mul"])
+@pytest.mark.parametrize("M,N,K", [(256, 528, 64), (257, 4112, 128), (511, 264, 192), (700, 2064, 4160)])
+def test_big_tiles(M, N, K, epi, w8):
+    _check(M, N, K, epi, w8)
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "w8"])
+@pytest.mark.parametrize("T", [65, 130, 200])
+def test_layer_rows(T, fp8):
+    """Decode layers of more than 64 rows whose QKV projection takes the first RMSNorm with it, against the oracle."""
+    shape = gen.LayerShape("mid", 2048, 16, 4, 128, 2064, 1e4)
+    rng = np.random.default_rng(T)
+    case = make_case(shape, gen.batch_decode(T, 1, 40, rng),
+                     weights=gen.make_weights_fp8(shape) if fp8 else None)
+    if fp8:
+        dense = {k: v for k, v in case.weights.items() if not k.startswith("s_")}
+        for k in ("qkv", "o", "gate_up", "down"):
+            w = case.weights["w_" + k].view(torch.float8_e4m3fn).float() * case.weights["s_" + k][:, None]
+            dense["w_" + k] = w.to(torch.bfloat16)
+    ref = make_case(shape, case.batch, weights=dense if fp8 else case.weights).run_oracle()[0]
+    dc = DevCase(case)
+    h = B.Handle(shape, T, T)
+    y = B.eb_layer_step_decode(h, dc.w, dc.k, dc.v, dc.bt, case.batch.context_lens, case.batch.chunk_lens, dc.x)
+    # 8-bit weights: the oracle's are rounded to bf16 once (2^-9 each), the kernel's codes and scales are not
+    assert maxrel(to_f32(y), ref) < 2e-2
