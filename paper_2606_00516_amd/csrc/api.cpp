@@ -158,7 +158,10 @@ hipError_t moe_second(const MoeArgs &a, hipStream_t st) {
 struct WsLayout {
   size_t meta = 0, act = 0, qkv = 0, attn = 0, h1 = 0, mlp = 0, part_o = 0, part_ml = 0, gemm = 0, alt = 0,
          moe = 0, ssq = 0, total = 0;
+  size_t gemm_max = (size_t)-1;  // split-K partials of one projection stay within this (plan_gemm)
 };
+
+constexpr int kMaxStreamSplits = 8;  // of a projection whose row sums of squares go to WsLayout::ssq
 
 // A decode-sized QKV projection (weight streaming with split K) takes the
 // first RMSNorm into its operand staging and its split-K sum into the RoPE /
@@ -185,28 +188,33 @@ WsLayout layout_for(const Shape &s, const HostPlan &p, bool full_step, bool stac
     L.attn = take(T * s.nq * s.hd * 2);
     L.h1 = take(T * s.hidden * 2);
     if (!s.moe()) L.mlp = take(T * s.ffn * 2);
-    size_t g = 0;
+    if (s.moe()) L.moe = take(moe_layout(p.T, s.hidden, s.ne, s.topk, s.effn).total);
+    // Batches of 65 to 255 rows split K into as many parts as they have CUs to
+    // fill, as long as the step still fits the fixed scratch of the entry point
+    // without a workspace (a batch that fits it with no partials at all is
+    // never refused for them); the same plan with any workspace, so that both
+    // entry points give the same bits.
     const int M = p.T;
+    const size_t least = off + align_up(T * sizeof(float));  // unsplit
+    const size_t rest = off + align_up(kMaxStreamSplits * T * sizeof(float));
+    if (M > 64 && M < 256 && least <= kNoAllocScratchBytes)
+      L.gemm_max = rest <= kNoAllocScratchBytes ? kNoAllocScratchBytes - rest : 0;
+    size_t g = 0, ss_splits = 1;
     // room for the plans of either weight type (the feed-forward ones when dense)
     for (int w8 = 0; w8 < 2; ++w8) {
       const int nplans = s.moe() ? 2 : 4;  // (an MoE layer has no dense feed-forward GEMMs)
       for (int i = 0; i < nplans; ++i) {
-        const GemmPlan gp = i == 0   ? plan_gemm(M, s.qkv_cols(), s.hidden, EPI_STORE, w8)
-                            : i == 1 ? plan_gemm(M, s.hidden, s.nq * s.hd, EPI_RESIDUAL, w8)
-                            : i == 2 ? plan_gemm(M, 2 * s.ffn, s.hidden, EPI_SILU_MUL, w8)
-                                     : plan_gemm(M, s.hidden, s.ffn, EPI_RESIDUAL, w8);
+        const GemmPlan gp = i == 0   ? plan_gemm(M, s.qkv_cols(), s.hidden, EPI_STORE, w8, L.gemm_max)
+                            : i == 1 ? plan_gemm(M, s.hidden, s.nq * s.hd, EPI_RESIDUAL, w8, L.gemm_max)
+                            : i == 2 ? plan_gemm(M, 2 * s.ffn, s.hidden, EPI_SILU_MUL, w8, L.gemm_max)
+                                     : plan_gemm(M, s.hidden, s.ffn, EPI_RESIDUAL, w8, L.gemm_max);
         g = gp.ws_bytes > g ? gp.ws_bytes : g;
+        // row sums of squares of the fused first RMSNorm (either weight type)
+        if (i == 0 && fused_qkv(gp) && (size_t)gp.splits > ss_splits) ss_splits = gp.splits;
       }
     }
-    if (s.moe()) L.moe = take(moe_layout(p.T, s.hidden, s.ne, s.topk, s.effn).total);
     L.gemm = take(g);
-    // row sums of squares of the fused first RMSNorm (either weight type)
-    int ss_splits = 1;
-    for (int w8 = 0; w8 < 2; ++w8) {
-      const GemmPlan qp = plan_gemm(M, s.qkv_cols(), s.hidden, EPI_STORE, w8);
-      if (fused_qkv(qp) && qp.splits > ss_splits) ss_splits = qp.splits;
-    }
-    L.ssq = take((size_t)ss_splits * T * sizeof(float));
+    L.ssq = take(ss_splits * T * sizeof(float));
     if (stack) L.alt = take(T * s.hidden * 2);
   }
   L.total = off;
@@ -424,7 +432,7 @@ static inline const uint16_t *pk(const void *p) { return static_cast<const uint1
 
 eb_status layer_body(eb_handle *h, const eb_layer_weights *w, const KV &kvd, const DevMeta &m, const StepBufs &B,
                      const uint16_t *xin, uint16_t *yout, int T, eb_mode mode, int layer, hipEvent_t *pev,
-                     hipStream_t st) {
+                     size_t gemm_max, hipStream_t st) {
   const Shape &sh = h->shape;
   const bool w8 = w->w_dtype == EB_W_FP8_E4M3;
   hipError_t e;
@@ -436,7 +444,7 @@ eb_status layer_body(eb_handle *h, const eb_layer_weights *w, const KV &kvd, con
   if ((e = mark(2 * (idx))) != hipSuccess) return hip_fail(e, "hipEventRecord"); \
   if ((e = (call)) != hipSuccess) return hip_fail(e, what);              \
   if ((e = mark(2 * (idx) + 1)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-  const GemmPlan qp = plan_gemm(T, sh.qkv_cols(), sh.hidden, EPI_STORE, w8);
+  const GemmPlan qp = plan_gemm(T, sh.qkv_cols(), sh.hidden, EPI_STORE, w8, gemm_max);
   const uint16_t *g1 = static_cast<const uint16_t *>(w->attn_norm);
   const uint16_t *gq = static_cast<const uint16_t *>(w->q_norm), *gk = static_cast<const uint16_t *>(w->k_norm);
   if (fused_qkv(qp)) {
@@ -464,7 +472,7 @@ eb_status layer_body(eb_handle *h, const eb_layer_weights *w, const KV &kvd, con
   // also writes RMSNorm(h1) * g2, and stage 6 has nothing left to do
   NormFuse nf{static_cast<const uint16_t *>(w->mlp_norm), B.act, sh.eps, false};
   EB_STAGE(5,
-           launch_gemm(plan_gemm(T, sh.hidden, sh.nq * sh.hd, EPI_RESIDUAL, w8), B.attn, w->w_o,
+           launch_gemm(plan_gemm(T, sh.hidden, sh.nq * sh.hd, EPI_RESIDUAL, w8, gemm_max), B.attn, w->w_o,
                        w8 ? w->s_o : nullptr, B.h1, xin, T, sh.hidden, sh.nq * sh.hd, EPI_RESIDUAL, B.gws, st, &nf,
                        w8 ? nullptr : pk(w->p_o)),
            "o gemm");
@@ -484,12 +492,12 @@ eb_status layer_body(eb_handle *h, const eb_layer_weights *w, const KV &kvd, con
     return EB_OK;
   }
   EB_STAGE(7,
-           launch_gemm(plan_gemm(T, 2 * sh.ffn, sh.hidden, EPI_SILU_MUL, w8), B.act, w->w_gate_up,
+           launch_gemm(plan_gemm(T, 2 * sh.ffn, sh.hidden, EPI_SILU_MUL, w8, gemm_max), B.act, w->w_gate_up,
                        w8 ? w->s_gate_up : nullptr, B.mlp, nullptr, T, 2 * sh.ffn, sh.hidden, EPI_SILU_MUL, B.gws,
                        st, nullptr, w8 ? nullptr : pk(w->p_gate_up)),
            "gate/up gemm");
   EB_STAGE(8,
-           launch_gemm(plan_gemm(T, sh.hidden, sh.ffn, EPI_RESIDUAL, w8), B.mlp, w->w_down,
+           launch_gemm(plan_gemm(T, sh.hidden, sh.ffn, EPI_RESIDUAL, w8, gemm_max), B.mlp, w->w_down,
                        w8 ? w->s_down : nullptr, yout, B.h1, T, sh.hidden, sh.ffn, EPI_RESIDUAL, B.gws, st, nullptr,
                        w8 ? nullptr : pk(w->p_down)),
            "down gemm");
@@ -543,7 +551,7 @@ eb_status run_layers(eb_handle *h, int32_t n_layers, const eb_layer_weights *w, 
   for (int l = 0; l < n_layers; ++l) {
     uint16_t *out = ((n_layers - 1 - l) % 2 == 0) ? static_cast<uint16_t *>(y) : B.alt;
     s = layer_body(h, &w[l], kv_of(&kv[l]), m, B, in, out, p.T, mode, l,
-                   slot >= 0 ? h->pslot[slot].data() : nullptr, st);
+                   slot >= 0 ? h->pslot[slot].data() : nullptr, L.gemm_max, st);
     if (s != EB_OK) return s;
     in = out;
   }

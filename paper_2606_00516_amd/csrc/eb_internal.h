@@ -113,13 +113,16 @@ hipError_t launch_attention(const Shape &s, const uint16_t *qkv, const KV &kv, c
 enum GemmEpi { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SILU_MUL = 2 };
 struct GemmPlan {
   int kind;      // 0 = weight-streaming, 1 = LDS-tiled, 2 = 256 x 256 tiles, -1 = none fits
-  int splits;    // split-K factor (skinny, and big with few tiles)
+  int splits;    // split-K factor (weight streaming, and big with few tiles)
   int kt_per;    // big: 64-wide K tiles per split
+  int bm;        // weight streaming: rows per block
   size_t ws_bytes;
 };
 // w8: W holds 8-bit E4M3 codes with one fp32 scale per row (launch_gemm's
 // wscale, null for bf16 weights); such plans never take the tiled kernel.
-GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8 = false);
+// max_ws: where the plan below 256 rows has no room for its partials there,
+// one that needs less is made.
+GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8 = false, size_t max_ws = (size_t)-1);
 // With nf, a residual GEMM whose plan splits K also writes the RMSNorm of
 // its result rows (gamma, out, eps) from the split-K sum and sets nf->done;
 // otherwise nf->done stays false and the caller runs the norm itself.

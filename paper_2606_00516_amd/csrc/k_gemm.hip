@@ -1409,8 +1409,8 @@ static int stream_bm(int M, int N, int K, bool w8) {
   return M <= 192 ? 192 : 256;
 }
 
-static int stream_splits(int M, int N, int K, bool w8) {
-  const int bm = stream_bm(M, N, K, w8);
+constexpr int kMaxSplits = 8;
+static int stream_splits(int M, int N, int K, int bm) {
   const int tiles = ((N + ST_BN - 1) / ST_BN) * ((M + bm - 1) / bm);
   const int nsteps = (K + 31) / 32;
   // one block per CU (256 CUs).  A grid that covers at least 3/4 of the CUs
@@ -1420,7 +1420,7 @@ static int stream_splits(int M, int N, int K, bool w8) {
   // once per split) and each split keeping 4 or more 128-wide K stages
   if (tiles >= 192) return 1;
   int best = 1;
-  for (int s = 2; s <= 8 && nsteps / s >= 16; ++s) {
+  for (int s = 2; s <= kMaxSplits && nsteps / s >= 16; ++s) {
     const long rs = ((long)tiles * s + 255) / 256, rb = ((long)tiles * best + 255) / 256;
     if (rs * best < rb * s) best = s;  // rs / s < rb / best
   }
@@ -1442,7 +1442,7 @@ static bool big_below_256(int M, int ncols, int K, bool w8) {
   return (ncols + ST_BN - 1) / ST_BN < 192 && ncols >= 8192 && K >= 8192;
 }
 
-GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8) {
+GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8, size_t max_ws) {
   GemmPlan p{};
   p.splits = 1;
   if (M <= 0 || N <= 0 || K <= 0) return p;  // nothing to plan (kind 0, no workspace)
@@ -1468,13 +1468,20 @@ GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8) {
     p.kt_per = (nk + splits - 1) / splits;
     p.splits = (nk + p.kt_per - 1) / p.kt_per;
     p.ws_bytes = p.splits > 1 ? (size_t)p.splits * M * ncols * sizeof(float) : 0;
-    return p;
+    if (M >= 256 || p.ws_bytes <= max_ws) return p;
   }
   // the weight-streaming kernels address both operands through 32-bit buffer ranges
   const bool sk_fits = (size_t)N * K * (w8 ? 1 : 2) < ((size_t)1 << 31) && (size_t)M * K * 2 < ((size_t)1 << 31);
   if ((M <= kStreamMaxRows || w8) && sk_fits) {  // (the tiled kernel reads bf16 weights only)
     p.kind = 0;
-    p.splits = stream_splits(M, ncols, K, w8);
+    p.bm = stream_bm(M, N, K, w8);
+    p.splits = stream_splits(M, ncols, K, p.bm);
+    const size_t one = (size_t)M * ncols * sizeof(float);
+    if (p.splits > 1 && p.splits * one > max_ws) {  // no room: blocks of 64 rows need fewer splits
+      p.bm = 64;
+      p.splits = stream_splits(M, ncols, K, 64);
+      while (p.splits > 1 && p.splits * one > max_ws) --p.splits;
+    }
     p.ws_bytes = p.splits > 1 ? (size_t)p.splits * M * ncols * sizeof(float) : 0;
     return p;
   }
@@ -1515,10 +1522,9 @@ static void launch_big(dim3 grid, hipStream_t st, const uint16_t *A, const void 
 
 template <bool PRENORM>
 static hipError_t launch_stream(const uint16_t *A, const void *W, const float *wscale, uint16_t *out,
-                                const uint16_t *res, float *part, int M, int N, int K, int epi, int splits,
+                                const uint16_t *res, float *part, int M, int N, int K, int epi, int splits, int bm,
                                 hipStream_t st, const uint16_t *gamma, float *ssq) {
   const bool w8 = wscale != nullptr;
-  const int bm = stream_bm(M, N, K, w8);
   const int ncols = logical_cols(N, epi);
   const int nsteps = (K + 31) / 32;
   const int per = (nsteps + splits - 1) / splits;
@@ -1566,7 +1572,7 @@ hipError_t launch_gemm(const GemmPlan &p, const uint16_t *A, const void *W, cons
     dim3 grid(8 * per_xcd, splits);
     if (!(Wp && packed_ok(N, K, epi) && M <= kPackedMaxRows)) {
       const hipError_t e =
-          launch_stream<false>(A, W, wscale, out, res, part, M, N, K, epi, splits, st, nullptr, nullptr);
+          launch_stream<false>(A, W, wscale, out, res, part, M, N, K, epi, splits, p.bm, st, nullptr, nullptr);
       if (e != hipSuccess || splits == 1) return e;
       return finish_splitk(part, splits, out, res, M, N, epi, nf, st);
     }
@@ -1617,7 +1623,8 @@ hipError_t launch_gemm_prenorm(const GemmPlan &p, const uint16_t *x, const uint1
   if (M <= 0) return hipSuccess;
   if (p.kind != 0 || p.splits < 2) return hipErrorInvalidValue;
   if (!(Wp && packed_ok(N, K, EPI_STORE) && M <= kPackedMaxRows))
-    return launch_stream<true>(x, W, wscale, nullptr, nullptr, part, M, N, K, (int)EPI_STORE, p.splits, st, gamma, ssq);
+    return launch_stream<true>(x, W, wscale, nullptr, nullptr, part, M, N, K, (int)EPI_STORE, p.splits, p.bm, st, gamma,
+                               ssq);
   const int nsteps = (K + 31) / 32;
   const int per = (nsteps + p.splits - 1) / p.splits;
   const int mt = (M + SK_BM - 1) / SK_BM;

@@ -90,3 +90,25 @@ def test_layer_rows(T, fp8):
     y = B.eb_layer_step_decode(h, dc.w, dc.k, dc.v, dc.bt, case.batch.context_lens, case.batch.chunk_lens, dc.x)
     # 8-bit weights: the oracle's are rounded to bf16 once (2^-9 each), the kernel's codes and scales are not
     assert maxrel(to_f32(y), ref) < 2e-2
+
+
+@pytest.mark.parametrize("T,ctx", [(129, 500), (252, 100), (252, 500), (252, 900)])
+def test_wide_decode_batch_fits_the_fixed_scratch(T, ctx):
+    """Batches of 129 to 255 rows split K further than their 64-row blocks would, but never out of the scratch of the
+    entry point without a workspace: what fits it without partials still does, with the bits of the regular step."""
+    shape = gen.L8B
+    rng = np.random.default_rng(T + ctx)
+    batch = gen.batch_decode(T, ctx - 50, ctx, rng)
+    w = gen.make_weights(shape, device="cuda")
+    pool = gen.make_kv_pool(shape, batch, device="cuda")
+    x = gen.make_x(shape, T, device="cuda")
+    h = B.Handle(shape, T, T)
+    assert B.eb_workspace_bytes(h, batch.context_lens, batch.chunk_lens, "mixed") <= B.eb_noalloc_scratch_bytes()
+    args = (h, w, pool.k_cache, pool.v_cache, pool.block_tables, batch.context_lens, batch.chunk_lens, x)
+    y = B.eb_layer_step_mixed(*args).clone()
+    assert torch.equal(y, B.eb_layer_step_mixed_noalloc(*args))
+    # the narrower plan's rows against the batch cut to 64 (its own splits)
+    n = 64
+    y64 = B.eb_layer_step_mixed(h, w, pool.k_cache, pool.v_cache, pool.block_tables[:n].contiguous(),
+                                batch.context_lens[:n], batch.chunk_lens[:n], x[:n].contiguous())
+    assert maxrel(to_f32(y[:n]), to_f32(y64)) < 1e-2
