@@ -109,8 +109,7 @@ struct MoeBufs {
   float *logits, *wts, *y;
   int32_t *ids, *offsets, *sorted_tok, *pos_of, *tiles, *n_tiles;
   uint16_t *m;
-  int max_tiles;
-  bool big;
+  int max_tiles, tile_rows;
 };
 MoeBufs moe_bufs(const MoeArgs &a) {
   const MoeLayout L = moe_layout(a.T, a.d, a.E, a.k, a.F);
@@ -126,29 +125,35 @@ MoeBufs moe_bufs(const MoeArgs &a) {
   B.m = reinterpret_cast<uint16_t *>(a.ws + L.m);
   B.y = reinterpret_cast<float *>(a.ws + L.y);
   B.max_tiles = L.max_tiles;
-  // experts with a few rows each (decode batches) stream their weights in
-  // 64-row tiles; with 128 or more rows per expert on average the 256 x 256
-  // kernel takes tiles of up to 256 rows
-  B.big = (long)a.T * a.k >= 128L * a.E && a.d % 64 == 0 && a.F % 64 == 0;
+  // experts with a few rows each (decode batches) stream their weights through
+  // tiles of 64 rows (tiles of 32 measured the same); from 80 rows per expert
+  // on average the 256 x 256 kernel takes tiles of up to 256 rows (gate/up +
+  // down on 128 experts of 768: 64 rows each 187 + 112 us streamed, 185 + 124
+  // in 256 x 256 tiles; 125 rows each 242 + 154 against 202 + 140)
+  B.tile_rows = (long)a.T * a.k >= 80L * a.E && a.d % 64 == 0 && a.F % 64 == 0 ? 256 : 64;
   return B;
+}
+hipError_t moe_products(const MoeBufs &B, const uint16_t *in, int in_rows, const int32_t *rows,
+                        const uint16_t *w, void *out, bool f32_out, int N, int K, int epi, hipStream_t st) {
+  if (B.tile_rows == 256)
+    return launch_gemm_grouped_big(in, in_rows, rows, w, out, f32_out, B.tiles, B.n_tiles, B.max_tiles, N, K, epi, st);
+  return launch_gemm_grouped(in, in_rows, rows, w, out, f32_out, B.tiles, B.n_tiles, B.max_tiles, N, K, epi, st);
 }
 hipError_t moe_first(const MoeArgs &a, hipStream_t st) {
   const MoeBufs B = moe_bufs(a);
-  auto grouped = B.big ? launch_gemm_grouped_big : launch_gemm_grouped;
   hipError_t e = launch_moe_route(a.b, a.w_router, a.T, a.d, a.E, a.k, a.renorm, B.logits, B.ids, B.wts, st);
+  // (the plan's counts use the down products' space: min(P / 1024 + 1, 256) E 4
+  // bytes against P d 4, with P >= 4096 and E <= 256)
   if (e == hipSuccess)
-    e = launch_moe_plan(B.ids, a.T * a.k, a.E, a.k, B.big ? 256 : 64, B.max_tiles, B.offsets, B.sorted_tok, B.pos_of,
-                        B.tiles, B.n_tiles, st);
+    e = launch_moe_plan(B.ids, a.T * a.k, a.E, a.k, B.tile_rows, B.max_tiles, B.offsets, B.sorted_tok, B.pos_of, B.tiles,
+                        B.n_tiles, reinterpret_cast<int32_t *>(B.y), st);
   if (e == hipSuccess)
-    e = grouped(a.b, a.T, B.sorted_tok, a.w_gate_up, B.m, false, B.tiles, B.n_tiles, B.max_tiles, 2 * a.F, a.d,
-                EPI_SILU_MUL, st);
+    e = moe_products(B, a.b, a.T, B.sorted_tok, a.w_gate_up, B.m, false, 2 * a.F, a.d, EPI_SILU_MUL, st);
   return e;
 }
 hipError_t moe_second(const MoeArgs &a, hipStream_t st) {
   const MoeBufs B = moe_bufs(a);
-  auto grouped = B.big ? launch_gemm_grouped_big : launch_gemm_grouped;
-  hipError_t e = grouped(B.m, a.T * a.k, nullptr, a.w_down, B.y, true, B.tiles, B.n_tiles, B.max_tiles, a.d, a.F,
-                         EPI_STORE, st);
+  hipError_t e = moe_products(B, B.m, a.T * a.k, nullptr, a.w_down, B.y, true, a.d, a.F, EPI_STORE, st);
   if (e == hipSuccess) e = launch_moe_combine(B.y, B.pos_of, B.wts, a.res, a.out, a.T, a.d, a.k, st);
   return e;
 }

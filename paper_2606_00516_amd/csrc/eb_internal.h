@@ -153,7 +153,8 @@ hipError_t launch_gemm_prenorm(const GemmPlan &p, const uint16_t *x, const uint1
 // expert-sorted rows (tables [3][max_tiles]: expert, first sorted row, rows;
 // *n_tiles of them in use) by their expert's W ([E][N][K] bf16), gathering A
 // rows through a_rows (null: the sorted row itself); SiLU epilogue to bf16
-// [rows, N / 2], or store to fp32 [rows, N] when f32_out.
+// [rows, N / 2], or store to fp32 [rows, N] when f32_out.  Tiles of up to
+// 64 rows.
 hipError_t launch_gemm_grouped(const uint16_t *A, int a_nrows, const int32_t *a_rows, const uint16_t *W, void *out,
                                bool f32_out, const int32_t *tiles, const int32_t *n_tiles, int max_tiles, int N, int K,
                                int epi, hipStream_t st);
@@ -161,10 +162,16 @@ hipError_t launch_gemm_grouped(const uint16_t *A, int a_nrows, const int32_t *a_
 hipError_t launch_gemm_grouped_big(const uint16_t *A, int a_nrows, const int32_t *a_rows, const uint16_t *W,
                                    void *out, bool f32_out, const int32_t *tiles, const int32_t *n_tiles, int max_tiles,
                                    int N, int K, int epi, hipStream_t st);
+// out fp32 [M, N] = A W^T on the weight-streaming kernel (bf16 operands under
+// 2 GiB, N and K multiples of 8).
+hipError_t launch_gemm_f32(const uint16_t *A, const uint16_t *W, float *out, int M, int N, int K, hipStream_t st);
+// scratch of launch_moe_plan: P >= 4096 assignments leave their experts'
+// counts of up to min(ceil(P / 1024), 256) blocks there, E int32 each.
 hipError_t launch_moe_route(const uint16_t *b, const uint16_t *wr, int T, int d, int E, int k, int renormalize,
                             float *logits, int32_t *ids, float *wts, hipStream_t st);
 hipError_t launch_moe_plan(const int32_t *ids, int P, int E, int k, int tile_rows, int max_tiles, int32_t *offsets,
-                           int32_t *sorted_tok, int32_t *pos_of, int32_t *tiles, int32_t *n_tiles, hipStream_t st);
+                           int32_t *sorted_tok, int32_t *pos_of, int32_t *tiles, int32_t *n_tiles, int32_t *scratch,
+                           hipStream_t st);
 hipError_t launch_moe_combine(const float *y, const int32_t *pos_of, const float *wts, const uint16_t *res,
                               uint16_t *out, int T, int d, int k, hipStream_t st);
 

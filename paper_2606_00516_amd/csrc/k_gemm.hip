@@ -83,19 +83,11 @@ __device__ __forceinline__ u32x4_t raw_rsrc(const void *base, uint32_t bytes) {
 }
 
 // ===========================================================================
-// weight streaming from a fragment-packed copy, and the tile constants that the
-// grouped kernel shares
+// weight streaming from a fragment-packed copy
 // ===========================================================================
-constexpr int SK_BN = 64;                // logical columns per block (grouped)
 constexpr int SK_BM = 64;                // rows per block
 constexpr int SK_KC = 128;               // K per stage
 constexpr int SK_ROWB = SK_KC * 2 + 16;  // LDS bytes per tile row (padded)
-constexpr int SK_LDS = 2 * (SK_BN + SK_BM) * SK_ROWB;
-
-// Logical column (0..63 in the block) of row j (0..15) of wave w's slice:
-// columns 8w..8w+7 and 32+8w..32+8w+7, so that a SiLU group's gate column
-// and its up partner (32 apart) land in the same wave.
-__device__ __forceinline__ int sk_col(int w, int j) { return j < 8 ? 8 * w + j : 32 + 8 * w + (j - 8); }
 
 // The packed weight-streaming kernel's block is 128 logical columns x 64
 // rows, one block per CU; each of the 4 waves owns 32 columns.
@@ -404,6 +396,16 @@ __global__ __launch_bounds__(256) void k_gemm_splitk_epilogue(const float *__res
   }
 }
 
+// Grouped use (the experts of a mixture-of-experts block): a row tile is some
+// expert-sorted rows of one expert (tables [3][max_tiles]: expert, first
+// sorted row, rows); its columns are those of that expert's W ([E][N][K]); A
+// rows are gathered through a_rows (null: the sorted row itself); the store
+// epilogue writes fp32.
+struct GroupedArgs {
+  const int32_t *a_rows, *tiles, *n_tiles;
+  int max_tiles, a_nrows, f32_out;
+};
+
 // ===========================================================================
 // stream: the weight-streaming kernel.  What bounds it is W's way from HBM,
 // so all of the CU's LDS is a ring of K stages loaded straight into it (no
@@ -422,13 +424,20 @@ __global__ __launch_bounds__(256) void k_gemm_splitk_epilogue(const float *__res
 // tile write each row's partial sum of squares over their K range to
 // ssq[split][M]; the row scale 1 / sqrt(mean(x^2) + eps) is applied to the
 // summed partials by the consumer (RMSNorm(x) g W^T = inv * ((x g) W^T)).
+//
+// GROUPED: the experts of a mixture-of-experts block with a few rows each.
+// Half the LDS per block, so that a block's start is hidden by its neighbour
+// (a block lasts 32 stages or less), an expert's column tiles side by side on
+// one XCD.  128 experts of 768 over hidden 2048, 64 tokens: gate/up 151 -> 134
+// us (6.0 TB/s), down 85 -> 73 against the register-staged 64 x 64 tiles it
+// replaced; 512 tokens 172 + 100 -> 147 + 84.
 // ===========================================================================
 constexpr int ST_BN = 128;  // logical columns per block
 // Rows per block, K per stage and ring depth: a stage holds 128 W rows and BM
 // A rows of KC values (bf16: 64, rows of 128 bytes; 8-bit W: 128, W rows of
 // 128 bytes of codes), the ring fills the CU's LDS (160 KiB less the norm
 // gains), all but one stage of it in flight.
-template <int BM, bool W8, bool PRENORM>
+template <int BM, bool W8, bool PRENORM, bool GROUPED = false>
 struct StreamTraits {
   static constexpr int KC = W8 ? 128 : 64;
   static constexpr int WROW = KC * (W8 ? 1 : 2);       // bytes of a W row
@@ -437,7 +446,7 @@ struct StreamTraits {
   static constexpr int A_BYTES = BM * AROW;
   static constexpr int G_BYTES = PRENORM ? 256 : 0;   // the stage's norm gains
   static constexpr int STAGE = W_BYTES + A_BYTES + G_BYTES;
-  static constexpr int R = (160 * 1024) / STAGE;
+  static constexpr int R = (GROUPED ? 80 * 1024 : 160 * 1024) / STAGE;  // (grouped: two blocks per CU)
   static constexpr int LDS = R * STAGE;
   static_assert(R >= 2, "ring depth");
   static constexpr int WM = BM >= 128 ? 2 : 1, WN = 4 / WM;  // wave grid
@@ -446,14 +455,14 @@ struct StreamTraits {
   static constexpr int LA = A_BYTES / 4096, LW = W_BYTES / 4096;  // load instructions per wave and stage
 };
 
-template <int BM, bool W8, bool PRENORM>
+template <int BM, bool W8, bool PRENORM, bool GROUPED = false>
 __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict__ A, const void *__restrict__ W,
                                                      const float *__restrict__ wscale, uint16_t *__restrict__ out,
                                                      const uint16_t *__restrict__ res, float *__restrict__ part, int M,
                                                      int N, int K, int epi, int ksteps_per_split, int tiles, int mt,
                                                      int per_xcd, const uint16_t *__restrict__ gamma,
-                                                     float *__restrict__ ssq) {
-  using Tr = StreamTraits<BM, W8, PRENORM>;
+                                                     float *__restrict__ ssq, GroupedArgs ga = GroupedArgs{}) {
+  using Tr = StreamTraits<BM, W8, PRENORM, GROUPED>;
   constexpr int KC = Tr::KC, R = Tr::R, NF = Tr::NF, NI = Tr::NI, LA = Tr::LA, LW = Tr::LW, AROW = Tr::AROW;
   constexpr int NL = LA + LW + (PRENORM ? 1 : 0);  // loads per wave and stage
   constexpr uint32_t WES = W8 ? 1u : 2u;
@@ -461,18 +470,36 @@ __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict_
   // block b takes tile (b % 8) * per_xcd + b / 8, so each XCD walks its own
   // contiguous tile range; the mt row blocks of one column tile are
   // neighbours there and share the W tile through that XCD's L2
+  // (grouped: mt column tiles per row tile, so an expert's tiles stay on one XCD)
+  if constexpr (GROUPED) {
+    tiles = __builtin_amdgcn_readfirstlane(*ga.n_tiles) * mt;
+    per_xcd = (tiles + 7) / 8;
+    if ((int)(blockIdx.x / 8) >= per_xcd) return;
+  }
   const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (t >= tiles) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = Tr::WM == 2 ? wave >> 1 : 0, wn = Tr::WM == 2 ? wave & 1 : wave;
-  const int n0 = (t / mt) * ST_BN, m0 = (t % mt) * BM;
+  const int ct = GROUPED ? t % mt : t / mt, nct = GROUPED ? mt : tiles / mt;  // column tile, of nct
+  const int n0 = ct * ST_BN;
+  int m0 = GROUPED ? 0 : (t % mt) * BM;
+  if constexpr (GROUPED) {  // the tile's rows as a matrix of its own: M rows, W and the outputs at their places
+    const int rt = t / mt;
+    const int e = __builtin_amdgcn_readfirstlane(ga.tiles[rt]);
+    const int row0 = __builtin_amdgcn_readfirstlane(ga.tiles[ga.max_tiles + rt]);
+    M = __builtin_amdgcn_readfirstlane(ga.tiles[2 * ga.max_tiles + rt]);
+    W = static_cast<const uint16_t *>(W) + (size_t)e * N * K;
+    if (part) part += (size_t)row0 * N;
+    if (out) out += (size_t)row0 * (epi == EPI_SILU_MUL ? N / 2 : N);
+    m0 = row0;  // (of the sorted rows, for the loads below)
+  }
   const int split = blockIdx.y;
   const int kbeg = split * ksteps_per_split * 32;
   const int kend = min(K, kbeg + ksteps_per_split * 32);
   const int nst = kend > kbeg ? (kend - kbeg + KC - 1) / KC : 0;
-  const uint32_t a_bytes = (uint32_t)min((size_t)M * K * 2, (size_t)0x7FFFFFFF);
+  const uint32_t a_bytes = (uint32_t)min((size_t)(GROUPED ? ga.a_nrows : M) * K * 2, (size_t)0x7FFFFFFF);
   const uint32_t w_bytes = (uint32_t)min((size_t)N * K * WES, (size_t)0x7FFFFFFF);
 
   // Loads.  A wave's load instruction i fills 1 KiB of LDS: rows of 128 bytes
@@ -494,14 +521,20 @@ __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict_
   }
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
-    const int m = m0 + (wave * LA + i) * RPI + lane / CPR;
-    aoff[i] = m < M ? (uint32_t)m * (uint32_t)K * 2u + (uint32_t)achunk(i) * 16u : 0x80000000u;
+    const int r = (wave * LA + i) * RPI + lane / CPR;
+    int m = GROUPED ? (r < M ? m0 + r : -1) : (m0 + r < M ? m0 + r : -1);
+    if constexpr (GROUPED) {
+      if (m >= 0 && ga.a_rows) m = ga.a_rows[m];
+      if (m >= ga.a_nrows) m = -1;
+    }
+    aoff[i] = m >= 0 ? (uint32_t)m * (uint32_t)K * 2u + (uint32_t)achunk(i) * 16u : 0x80000000u;
   }
+  if constexpr (GROUPED) m0 = 0;  // the outputs' rows
   const u32x4_t ra = raw_rsrc(A, a_bytes), rw = raw_rsrc(W, w_bytes);
   const u32x4_t rg = raw_rsrc(PRENORM ? gamma : A, PRENORM ? (uint32_t)K * 2u : 0u);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)st_lds;
   // stage s into the ring slot at byte `slot`
-  const int rot = gridDim.y == 1 ? k_start(t / mt, tiles / mt, (kend - kbeg + 127) / 128) * (128 / KC) : 0;
+  const int rot = gridDim.y == 1 ? k_start(ct, nct, (kend - kbeg + 127) / 128) * (128 / KC) : 0;
   auto issue = [&](int s, uint32_t slot) {
     const int k0 = s >= nst ? kend : kbeg + (s + rot < nst ? s + rot : s + rot - nst) * KC;
     const uint32_t dw = lds0 + slot + (uint32_t)(wave * LW) * 1024u;
@@ -858,16 +891,6 @@ constexpr int BG_HALF_BYTES = BG_TILE_BYTES / 2;
 
 __device__ __forceinline__ int bg_swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
-// Grouped use (the experts of a mixture-of-experts block): a tile is up to
-// 256 expert-sorted rows of one expert (tables [3][max_tiles]: expert, first
-// sorted row, rows); block b takes tile b / tiles_n and column tile
-// b % tiles_n of that expert's W ([E][N][K]); A rows are gathered through
-// a_rows (null: the sorted row itself); the store epilogue may write fp32.
-struct GroupedArgs {
-  const int32_t *a_rows, *tiles, *n_tiles;
-  int max_tiles, a_nrows, f32_out;
-};
-
 template <int epi, bool W8, bool GROUPED>
 __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restrict__ A, const void *__restrict__ W,
                                                          const float *__restrict__ wscale, uint16_t *__restrict__ out,
@@ -1150,139 +1173,6 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
 }
 
 // ===========================================================================
-// grouped: the experts of a mixture-of-experts block
-// ===========================================================================
-// Rows are sorted by expert; a row tile is up to 64 consecutive sorted rows of
-// one expert (tile tables: expert, first sorted row, rows).  Block b takes row
-// tile b / col_tiles and column tile b % col_tiles of that expert's W, so the
-// column tiles of one row tile run side by side and share its A rows, and
-// the row tiles of one expert follow each other and share its W tiles in L2.
-// The main loop stages W and A through LDS in 128-wide K slices as the
-// weight-streaming kernel does; here the 4 waves split the tile's 64 columns
-// (16 each, transposed product).  A rows are gathered through a_rows (null: the sorted row
-// itself).  SiLU: bf16 [rows, N / 2]; store: fp32 [rows, N].
-template <bool F32OUT>
-__global__ __launch_bounds__(256) void k_gemm_grouped(const uint16_t *__restrict__ A, int a_nrows,
-                                                      const int32_t *__restrict__ a_rows,
-                                                      const uint16_t *__restrict__ W, void *__restrict__ out,
-                                                      const int32_t *__restrict__ tiles,
-                                                      const int32_t *__restrict__ n_tiles, int max_tiles, int N,
-                                                      int K, int epi, int col_tiles) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t gg_lds[];  // [2][64 W rows + 64 A rows][SK_ROWB]
-  const int rt = blockIdx.x / col_tiles, ct = blockIdx.x % col_tiles;
-  if (rt >= __builtin_amdgcn_readfirstlane(*n_tiles)) return;
-  const int e = __builtin_amdgcn_readfirstlane(tiles[rt]);
-  const int row0 = __builtin_amdgcn_readfirstlane(tiles[max_tiles + rt]);
-  const int rows = __builtin_amdgcn_readfirstlane(tiles[2 * max_tiles + rt]);
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n0 = ct * SK_BN;
-  const int nst = (K + SK_KC - 1) / SK_KC;
-  const uint16_t *We = W + (size_t)e * N * K;
-  const buf_rsrc_t ra = make_rsrc(A, (int)min((size_t)a_nrows * K * 2, (size_t)0x7FFFFFFF));
-  const buf_rsrc_t rw = make_rsrc(We, (int)min((size_t)N * K * 2, (size_t)0x7FFFFFFF));
-
-  // staging as in the weight-streaming kernel: thread t moves 16-byte chunk
-  // t % 16 of tile rows t / 16 + 16 j; rows outside the tile or the operands
-  // and k past K load zeros without memory traffic
-  const int ch = tid & 15, r0 = tid >> 4;
-  uint32_t woff[4], aoff[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int wr = w_row_of(n0 + r0 + 16 * j, N, epi);
-    woff[j] = wr >= 0 ? ((uint32_t)wr * (uint32_t)K + (uint32_t)(ch * 8)) * 2u : 0x80000000u;
-    const int r = r0 + 16 * j;
-    const int ar = r < rows ? (a_rows ? a_rows[row0 + r] : row0 + r) : -1;
-    aoff[j] = ar >= 0 && ar < a_nrows ? ((uint32_t)ar * (uint32_t)K + (uint32_t)(ch * 8)) * 2u : 0x80000000u;
-  }
-  u32x4_t wa[4], aa[4], wb[4], ab[4];
-  auto gload = [&](int s, u32x4_t (&wr)[4], u32x4_t (&ar)[4]) {
-    const int k = s * SK_KC + ch * 8;
-    const bool ok = s < nst && k < K;
-    const uint32_t kb = (uint32_t)(s * SK_KC) * 2u;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      wr[j] = buf_ld_u32x4<kAuxNT>(rw, (int)(ok ? woff[j] + kb : 0x80000000u));
-      ar[j] = buf_ld_u32x4<0>(ra, (int)(ok ? aoff[j] + kb : 0x80000000u));
-    }
-  };
-  auto swrite = [&](int buf, const u32x4_t (&wr)[4], const u32x4_t (&ar)[4]) {
-    uint8_t *b = gg_lds + buf * (SK_BN + SK_BM) * SK_ROWB;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      *reinterpret_cast<u32x4_t *>(b + (r0 + 16 * j) * SK_ROWB + ch * 16) = wr[j];
-      *reinterpret_cast<u32x4_t *>(b + (SK_BN + r0 + 16 * j) * SK_ROWB + ch * 16) = ar[j];
-    }
-  };
-  f32x4_t acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const int lr = lane & 15, lg = lane >> 4;
-  const int my_wrow = sk_col(wave, lr);
-  auto compute = [&](int buf) {
-    const uint8_t *b = gg_lds + buf * (SK_BN + SK_BM) * SK_ROWB;
-#pragma unroll
-    for (int ks = 0; ks < SK_KC / 32; ++ks) {
-      const u32x4_t wf = *reinterpret_cast<const u32x4_t *>(b + my_wrow * SK_ROWB + (ks * 4 + lg) * 16);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const u32x4_t af = *reinterpret_cast<const u32x4_t *>(b + (SK_BN + i * 16 + lr) * SK_ROWB + (ks * 4 + lg) * 16);
-        acc[i] = mfma16x16x32(wf, af, acc[i]);
-      }
-    }
-  };
-  gload(0, wa, aa);
-  swrite(0, wa, aa);
-  gload(1, wa, aa);
-  gload(2, wb, ab);
-  __syncthreads();
-  for (int st = 0; st < nst; st += 2) {
-    compute(0);
-    swrite(1, wa, aa);
-    gload(st + 3, wa, aa);
-    __syncthreads();
-    if (st + 1 >= nst) break;
-    compute(1);
-    swrite(0, wb, ab);
-    gload(st + 4, wb, ab);
-    __syncthreads();
-  }
-
-  // lane: tile rows 16 i + lr, logical columns c .. c + 3, c = sk_col(wave, 4 lg)
-  const int c = sk_col(wave, 4 * lg);
-  if (epi == EPI_SILU_MUL) {
-    const int F = N >> 1;
-    const int f = (n0 >> 1) + 8 * wave + 4 * lg;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f32x4_t u;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) u[q] = shfl_xor_f32(acc[i][q], 32);
-      const int m = i * 16 + lr;
-      if (!F32OUT && lg < 2 && m < rows && f < F) {
-        const u32x2_t w = {pack_bf16x2(silu_f(acc[i][0]) * u[0], silu_f(acc[i][1]) * u[1]),
-                           pack_bf16x2(silu_f(acc[i][2]) * u[2], silu_f(acc[i][3]) * u[3])};
-        *reinterpret_cast<u32x2_t *>(static_cast<uint16_t *>(out) + (size_t)(row0 + m) * F + f) = w;
-      }
-    }
-    return;
-  }
-  const int n = n0 + c;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = i * 16 + lr;
-    if (m < rows && n < N) {
-      if constexpr (F32OUT)
-        *reinterpret_cast<f32x4_t *>(static_cast<float *>(out) + (size_t)(row0 + m) * N + n) = acc[i];
-      else
-        *reinterpret_cast<u32x2_t *>(static_cast<uint16_t *>(out) + (size_t)(row0 + m) * N + n) =
-            u32x2_t{pack_bf16x2(acc[i][0], acc[i][1]), pack_bf16x2(acc[i][2], acc[i][3])};
-    }
-  }
-}
-
-// ===========================================================================
 // planning and launch
 // ===========================================================================
 // Row counts up to this use the weight-streaming kernels.
@@ -1553,6 +1443,10 @@ static hipError_t launch_stream(const uint16_t *A, const void *W, const float *w
   return hipGetLastError();
 }
 
+hipError_t launch_gemm_f32(const uint16_t *A, const uint16_t *W, float *out, int M, int N, int K, hipStream_t st) {
+  return launch_stream<false>(A, W, nullptr, nullptr, nullptr, out, M, N, K, (int)EPI_STORE, 1, 64, st, nullptr, nullptr);
+}
+
 hipError_t launch_gemm(const GemmPlan &p, const uint16_t *A, const void *W, const float *wscale, uint16_t *out,
                        const uint16_t *res, int M, int N, int K, int epi, void *ws, hipStream_t st, NormFuse *nf,
                        const uint16_t *Wp) {
@@ -1652,14 +1546,14 @@ hipError_t launch_gemm_grouped(const uint16_t *A, int a_nrows, const int32_t *a_
                                bool f32_out, const int32_t *tiles, const int32_t *n_tiles, int max_tiles, int N, int K,
                                int epi, hipStream_t st) {
   if (max_tiles <= 0) return hipSuccess;
-  const int col_tiles = (logical_cols(N, epi) + SK_BN - 1) / SK_BN;
-  const dim3 grid((unsigned)max_tiles * (unsigned)col_tiles);
-  if (f32_out)
-    hipLaunchKernelGGL(k_gemm_grouped<true>, grid, dim3(256), SK_LDS, st, A, a_nrows, a_rows, W, out, tiles, n_tiles,
-                       max_tiles, N, K, epi, col_tiles);
-  else
-    hipLaunchKernelGGL(k_gemm_grouped<false>, grid, dim3(256), SK_LDS, st, A, a_nrows, a_rows, W, out, tiles,
-                       n_tiles, max_tiles, N, K, epi, col_tiles);
+  const int nct = (logical_cols(N, epi) + ST_BN - 1) / ST_BN;
+  const unsigned grid = ((unsigned)max_tiles * (unsigned)nct + 7) / 8 * 8;
+  const GroupedArgs ga{a_rows, tiles, n_tiles, max_tiles, a_nrows, f32_out ? 1 : 0};
+  uint16_t *o16 = f32_out ? nullptr : static_cast<uint16_t *>(out);
+  float *o32 = f32_out ? static_cast<float *>(out) : nullptr;
+  hipLaunchKernelGGL((k_gemm_stream<64, false, false, true>), dim3(grid), dim3(256),
+                     (StreamTraits<64, false, false, true>::LDS), st, A, W, nullptr, o16, nullptr, o32, 0, N, K, epi,
+                     (K + 31) / 32, 0, nct, 0, nullptr, nullptr, ga);
   return hipGetLastError();
 }
 
