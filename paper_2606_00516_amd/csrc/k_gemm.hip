@@ -416,8 +416,15 @@ struct GroupedArgs {
 // barrier: 64 rows, qkv 22.3 -> 17.8 us, gate/up 51.2 -> 43.3; 8-bit W at 37
 // rows, gate/up 41.0 -> 28.1, down 24.7 -> 20.4; more rows: stream_bm.
 //
-// Wave grid: 1 x 4 (32 columns a wave, all rows) to 64 rows, 2 x 2 (64
-// columns, half the rows) above, which halves the LDS reads per product.
+// Eight waves, two on each SIMD, so that one issues loads or waits while the
+// other multiplies (four waves, one a SIMD, before: 8-bit W at 37 rows, gate/up
+// 28.5 -> 26.9 us, down 21.2 -> 20.0; 160 rows, qkv 26.2 -> 25.0, O 22.5 -> 21.6;
+// 240 rows, gate/up 74 -> 71).  Wave grid: 2 x 4 (32 columns a wave, half the rows) to 64 rows, 4 x
+// 2 (64 columns, a quarter of the rows) above, which reads each W fragment
+// from LDS for fewer waves.  Measured and not taken: a ring of its own for W
+// and for A, W's deeper, loaded by half of the waves each (one wave then
+// issues twice the loads per stage: 8B O and down slower by 3 to 5 %).
+//
 // PRENORM (split-K partials only): A holds the rows x of an RMSNorm that
 // precedes the product.  A landed stage's rows become bf16(x * gamma) in place
 // one stage before they are multiplied, and the blocks of the first column
@@ -449,19 +456,20 @@ struct StreamTraits {
   static constexpr int R = (GROUPED ? 80 * 1024 : 160 * 1024) / STAGE;  // (grouped: two blocks per CU)
   static constexpr int LDS = R * STAGE;
   static_assert(R >= 2, "ring depth");
-  static constexpr int WM = BM >= 128 ? 2 : 1, WN = 4 / WM;  // wave grid
+  static constexpr int NW = GROUPED ? 4 : 8;          // waves: two on each SIMD (grouped: one of each of two blocks)
+  static constexpr int WM = GROUPED ? 1 : BM >= 128 ? 4 : 2, WN = NW / WM;  // wave grid
   static constexpr int NF = ST_BN / WN / 16;          // 16-column fragments per wave
   static constexpr int NI = BM / WM / 16;             // 16-row blocks per wave
-  static constexpr int LA = A_BYTES / 4096, LW = W_BYTES / 4096;  // load instructions per wave and stage
+  static constexpr int LA = A_BYTES / (NW * 1024), LW = W_BYTES / (NW * 1024);  // load instructions per wave and stage
+  static_assert(LA * NW * 1024 == A_BYTES && LW * NW * 1024 == W_BYTES && NI * WM * 16 == BM, "wave shares");
 };
 
 template <int BM, bool W8, bool PRENORM, bool GROUPED = false>
-__global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict__ A, const void *__restrict__ W,
-                                                     const float *__restrict__ wscale, uint16_t *__restrict__ out,
-                                                     const uint16_t *__restrict__ res, float *__restrict__ part, int M,
-                                                     int N, int K, int epi, int ksteps_per_split, int tiles, int mt,
-                                                     int per_xcd, const uint16_t *__restrict__ gamma,
-                                                     float *__restrict__ ssq, GroupedArgs ga = GroupedArgs{}) {
+__global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) void k_gemm_stream(
+    const uint16_t *__restrict__ A, const void *__restrict__ W, const float *__restrict__ wscale,
+    uint16_t *__restrict__ out, const uint16_t *__restrict__ res, float *__restrict__ part, int M, int N, int K, int epi,
+    int ksteps_per_split, int tiles, int mt, int per_xcd, const uint16_t *__restrict__ gamma, float *__restrict__ ssq,
+    GroupedArgs ga = GroupedArgs{}) {
   using Tr = StreamTraits<BM, W8, PRENORM, GROUPED>;
   constexpr int KC = Tr::KC, R = Tr::R, NF = Tr::NF, NI = Tr::NI, LA = Tr::LA, LW = Tr::LW, AROW = Tr::AROW;
   constexpr int NL = LA + LW + (PRENORM ? 1 : 0);  // loads per wave and stage
@@ -481,7 +489,7 @@ __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict_
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = Tr::WM == 2 ? wave >> 1 : 0, wn = Tr::WM == 2 ? wave & 1 : wave;
+  const int wm = wave / Tr::WN, wn = wave % Tr::WN;
   const int ct = GROUPED ? t % mt : t / mt, nct = GROUPED ? mt : tiles / mt;  // column tile, of nct
   const int n0 = ct * ST_BN;
   int m0 = GROUPED ? 0 : (t % mt) * BM;
@@ -539,7 +547,7 @@ __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict_
     const int k0 = s >= nst ? kend : kbeg + (s + rot < nst ? s + rot : s + rot - nst) * KC;
     const uint32_t dw = lds0 + slot + (uint32_t)(wave * LW) * 1024u;
     const uint32_t da = lds0 + slot + Tr::W_BYTES + (uint32_t)(wave * LA) * 1024u;
-    if constexpr (PRENORM) {  // (the four waves write the same values)
+    if constexpr (PRENORM) {  // (all waves write the same values)
       const uint32_t go = (uint32_t)(k0 * 2 + lane * 4);
       dma_lds4(rg, k0 < kend ? go : 0x80000000u, 0u, lds0 + slot + Tr::W_BYTES + Tr::A_BYTES);
     }
@@ -597,19 +605,19 @@ __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict_
   };
   // PRENORM: the A rows of a landed stage become bf16(x * gain) in place, the
   // blocks of the first column tile adding up their squares on the way
-  constexpr int TJ = Tr::A_BYTES / 4096;
+  constexpr int NT = 64 * Tr::NW, TJ = Tr::A_BYTES / (NT * 16);
   float ssacc[TJ];
 #pragma unroll
   for (int j = 0; j < TJ; ++j) ssacc[j] = 0.f;
   const bool first_col_tile = n0 == 0;
   auto prenorm = [&](uint32_t slot) {
-    const int p = tid % CPR, row = tid / CPR;  // rows + (256 / CPR) j: the same chunk for all j
+    const int p = tid % CPR, row = tid / CPR;  // rows + (NT / CPR) j: the same chunk for all j
     const int c = swz(row, p, AROW);
     uint8_t *a = st_lds + slot + Tr::W_BYTES + row * AROW + p * 16;
     const u32x4_t g = *reinterpret_cast<const u32x4_t *>(st_lds + slot + Tr::W_BYTES + Tr::A_BYTES + c * 16);
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
-      u32x4_t x = *reinterpret_cast<const u32x4_t *>(a + j * 4096);
+      u32x4_t x = *reinterpret_cast<const u32x4_t *>(a + j * NT * 16);
       if (first_col_tile) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -619,7 +627,7 @@ __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict_
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) x[e] = pack_bf16x2(bf16_lo(x[e]) * bf16_lo(g[e]), bf16_hi(x[e]) * bf16_hi(g[e]));
-      *reinterpret_cast<u32x4_t *>(a + j * 4096) = x;
+      *reinterpret_cast<u32x4_t *>(a + j * NT * 16) = x;
     }
   };
 
@@ -655,7 +663,7 @@ __global__ __launch_bounds__(256) void k_gemm_stream(const uint16_t *__restrict_
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
         const float v = group_sum<CPR>(ssacc[j]);
-        const int m = m0 + tid / CPR + (256 / CPR) * j;
+        const int m = m0 + tid / CPR + (NT / CPR) * j;
         if (tid % CPR == 0 && m < M) ssq[(size_t)split * M + m] = v;
       }
     }
@@ -1423,8 +1431,8 @@ static hipError_t launch_stream(const uint16_t *A, const void *W, const float *w
   const int per_xcd = (tiles + 7) / 8;
   const dim3 grid(8 * per_xcd, splits);
 #define EB_STREAM(BM_, W8_)                                                                                         \
-  hipLaunchKernelGGL((k_gemm_stream<BM_, W8_, PRENORM>), grid, dim3(256), (StreamTraits<BM_, W8_, PRENORM>::LDS), st, A, \
-                     W, wscale, out, res, part, M, N, K, epi, per, tiles, mt, per_xcd, gamma, ssq)
+  hipLaunchKernelGGL((k_gemm_stream<BM_, W8_, PRENORM>), grid, dim3(64 * StreamTraits<BM_, W8_, PRENORM>::NW),       \
+                     (StreamTraits<BM_, W8_, PRENORM>::LDS), st, A, W, wscale, out, res, part, M, N, K, epi, per, tiles, mt, per_xcd, gamma, ssq)
   if (w8) {
     if (bm == 64)
       EB_STREAM(64, true);
