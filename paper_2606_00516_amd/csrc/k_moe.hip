@@ -226,7 +226,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_moe_plan(const int32_t *__rest
 // the token's positions and weights are fetched first, then the rows of
 // eight experts are in flight together (the sum keeps the experts' order; a
 // loop that waited for each position, then its row, read 8192 tokens' 537 MB
-// in 146 us, this one in 138; 64 tokens 7.6 -> 4.8).
+// in 146 us, this one in 138; 64 tokens 7.6 -> 4.8).  y is read once and, at
+// thousands of tokens, larger than the caches: non-temporal loads leave them
+// to the positions and the output (8192 tokens 137 -> 108 us, 5.6 TB/s; 64
+// tokens, whose y does fit, 4.9 both).
 __global__ __launch_bounds__(256) void k_moe_combine(const float *__restrict__ y, const int32_t *__restrict__ pos_of,
                                                      const float *__restrict__ wts, const uint16_t *__restrict__ res,
                                                      uint16_t *__restrict__ out, int d, int k) {
@@ -245,7 +248,8 @@ __global__ __launch_bounds__(256) void k_moe_combine(const float *__restrict__ y
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       if (j0 + u < k)
-        v[u] = *reinterpret_cast<const f32x4_t *>(y + (size_t)__builtin_amdgcn_readlane(pv, j0 + u) * d + c);
+        v[u] = __builtin_nontemporal_load(
+            reinterpret_cast<const f32x4_t *>(y + (size_t)__builtin_amdgcn_readlane(pv, j0 + u) * d + c));
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       if (j0 + u < k) acc += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wv), j0 + u)) * v[u];
