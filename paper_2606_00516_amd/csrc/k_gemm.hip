@@ -132,7 +132,7 @@ __global__ __launch_bounds__(256) void k_pack_weight(const uint16_t *__restrict_
   *reinterpret_cast<u32x4_t *>(P + q * 8) = *reinterpret_cast<const u32x4_t *>(W + row * K + k);
 }
 
-// The weight-streaming kernel on packed bf16 weights.  Same block, columns,
+// The weight-streaming kernel on packed bf16 weights (four waves).  Same columns,
 // split ranges, products and epilogues as k_gemm_stream<64, false>, but each
 // wave loads its W operands straight into registers from the packed copy
 // (every element of W is used by one wave only, so W needs no LDS), three
