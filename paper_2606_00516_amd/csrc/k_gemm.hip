@@ -556,7 +556,7 @@ __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) 
       for (int i = 0; i < LA; ++i) dma_lds16(ra, aoff[i], (uint32_t)k0 * 2u, da + i * 1024);
 #pragma unroll
       for (int i = 0; i < LW; ++i) dma_lds16(rw, woff[i], (uint32_t)k0 * WES, dw + i * 1024);
-    } else {  // the last stage of a ragged range, or past it
+    } else {  // the last stage of a ragged range, or past it (8-bit W: see clear_tail)
 #pragma unroll
       for (int i = 0; i < LA; ++i)
         dma_lds16(ra, k0 + achunk(i) * 8 < kend && aoff[i] != 0x80000000u ? aoff[i] + (uint32_t)k0 * 2u : 0x80000000u, 0u,
@@ -602,6 +602,16 @@ __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) 
           for (int i = 0; i < NI; ++i) acc[f][i] = mfma16x16x32(wf[f], af[i], acc[f][i]);
       }
     }
+  };
+  // 8-bit W whose K ends 8 codes into a 16-code chunk: the chunk's other 8
+  // are the next W row's first codes.  A is zero there, but a NaN code times
+  // zero is NaN, so they are cleared in the landed stage before its products.
+  const int tail_stage = W8 && (kend & 8) ? nst - 1 - rot : -1;  // walk position of the range's last stage
+  auto clear_tail = [&](uint32_t slot) {
+    const int c = ((kend - kbeg) % KC) / CK;  // (ranges begin at multiples of 32)
+    if (tid < ST_BN) *reinterpret_cast<u32x2_t *>(st_lds + slot + tid * WROW + (swz(tid, c, WROW) << 4) + 8) = u32x2_t{0u, 0u};
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wave_barrier();
   };
   // PRENORM: the A rows of a landed stage become bf16(x * gain) in place, the
   // blocks of the first column tile adding up their squares on the way
@@ -654,6 +664,9 @@ __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) 
     issue(s + R - 1, fill);
     fill = next(fill);
     if constexpr (PRENORM) prenorm(next(slot));
+    if constexpr (W8) {
+      if (s == tail_stage) clear_tail(slot);
+    }
     compute(slot);
     slot = next(slot);
   }

@@ -56,6 +56,26 @@ def test_stream_rows(M, N, K, w8):
     _check(M, N, K, "store" if M % 2 else "residual", w8)
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 4104, 1032), (64, 264, 520), (65, 4104, 1032), (128, 8208, 1048),
+                                   (300, 1032, 2056), (37, 28688, 264)])
+def test_nan_codes_stay_in_their_row(M, N, K):
+    """NaN codes (0x7F, 0xFF) in the first 8 columns of some weight rows, with a K that ends 8 codes into a 16-code
+    chunk, whose other half is the next row's start: exactly those rows' output columns are NaN, the others keep the
+    bits of a matrix without them."""
+    A = torch.randn(M, K, device="cuda").to(torch.bfloat16)
+    W, s = gen.make_fp8_matrix(N, K, 3, device="cuda", proj_std=0.05)
+    clean = B.eb_op_gemm_w8(A, W, s)
+    rows = torch.tensor([1, 2, 17, 130, N - 1], device="cuda")
+    W = W.clone()
+    W[rows, torch.tensor([0, 7, 3, 5, 6], device="cuda")] = torch.tensor([0x7F, 0xFF, 0x7F, 0xFF, 0x7F],
+                                                                         dtype=torch.uint8, device="cuda")
+    got = B.eb_op_gemm_w8(A, W, s)
+    bad = torch.zeros(N, dtype=torch.bool, device="cuda")
+    bad[rows] = True
+    assert torch.isnan(got[:, bad]).all()
+    assert torch.equal(got[:, ~bad], clean[:, ~bad])
+
+
 @pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
 @pytest.mark.parametrize("M,N,K", [(33, 28688, 512), (100, 28688, 512), (180, 28688, 264), (240, 28688, 1152),
                                    (64, 25600, 136), (130, 1376, 256)])
