@@ -547,9 +547,11 @@ __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) 
     const int k0 = s >= nst ? kend : kbeg + (s + rot < nst ? s + rot : s + rot - nst) * KC;
     const uint32_t dw = lds0 + slot + (uint32_t)(wave * LW) * 1024u;
     const uint32_t da = lds0 + slot + Tr::W_BYTES + (uint32_t)(wave * LA) * 1024u;
-    if constexpr (PRENORM) {  // (all waves write the same values)
-      const uint32_t go = (uint32_t)(k0 * 2 + lane * 4);
-      dma_lds4(rg, k0 < kend ? go : 0x80000000u, 0u, lds0 + slot + Tr::W_BYTES + Tr::A_BYTES);
+    if constexpr (PRENORM) {
+      // (all waves write the same values; gains past the range are zero like
+      // the rows they meet there: an infinite one would make a NaN of them)
+      const int k = k0 + 2 * lane;
+      dma_lds4(rg, k < kend ? (uint32_t)(k * 2) : 0x80000000u, 0u, lds0 + slot + Tr::W_BYTES + Tr::A_BYTES);
     }
     if (k0 + KC <= kend) {
 #pragma unroll

@@ -112,6 +112,30 @@ def test_layer_rows(T, fp8):
     assert maxrel(to_f32(y), ref) < 2e-2
 
 
+@pytest.mark.parametrize("T", [3, 70])
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "w8"])
+def test_infinite_gain_stays_in_its_k_range(T, fp8):
+    """An infinite first-norm gain at every multiple of 32, so at the first column of each K split too, where the split
+    before may end inside a stage: the v rows are infinite (one infinite term each), never NaN."""
+    shape = gen.LayerShape("wide-qkv", 2048, 64, 8, 128, 256, 1e4)
+    batch = gen.batch_decode(T, 1, 40, np.random.default_rng(T))
+    case = make_case(shape, batch, weights=gen.make_weights_fp8(shape) if fp8 else None)
+    if not fp8:   # (a zero would make the term NaN by itself)
+        case.weights["w_qkv"][case.weights["w_qkv"] == 0] = 2.0 ** -10
+    case.x[case.x == 0] = 2.0 ** -10
+    dc = DevCase(case)
+    h = B.Handle(shape, T, T)
+    pos = torch.as_tensor(batch.context_lens, device="cuda").long()
+    page = dc.bt[torch.arange(T, device="cuda"), pos // 16].long()
+    gain = dc.w["attn_norm"].clone()
+    for k in range(0, shape.hidden, 32):
+        dc.w["attn_norm"].copy_(gain)
+        dc.w["attn_norm"][k] = float("inf")
+        B.eb_layer_step_decode(h, dc.w, dc.k, dc.v, dc.bt, batch.context_lens, batch.chunk_lens, dc.x)
+        new = dc.v[page, :, pos % 16].float()
+        assert torch.isinf(new).all(), (k, torch.isnan(new).sum().item())
+
+
 @pytest.mark.parametrize("T,ctx", [(129, 500), (252, 100), (252, 500), (252, 900)])
 def test_wide_decode_batch_fits_the_fixed_scratch(T, ctx):
     """Batches of 129 to 255 rows split K further than their 64-row blocks would, but never out of the scratch of the
