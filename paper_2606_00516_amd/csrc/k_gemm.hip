@@ -38,8 +38,10 @@ __host__ __device__ static inline int logical_cols(int N, int epi) {
   return ((F + 31) / 32) * 64;
 }
 
-// (the reciprocal instruction is good to one unit in the last place of fp32)
-__device__ __forceinline__ float silu_f(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
+// (a division: the reciprocal instruction is one unit in the last place less
+// exact, and its result is flushed to zero for g below -87.3, where the value
+// is still a normal bf16)
+__device__ __forceinline__ float silu_f(float g) { return g / (1.0f + __expf(-g)); }
 
 // 8-bit weights: the fp32 sums of logical columns c .. c + 3 (one W row
 // each, consecutive within a column group) times their rows' scales.

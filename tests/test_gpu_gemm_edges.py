@@ -85,6 +85,30 @@ def test_stream_silu(M, N, K, w8):
 
 
 @pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
+@pytest.mark.parametrize("M", [40, 100, 300])
+def test_silu_at_the_end_of_its_range(M, w8):
+    """Gates from -88.5 to -80 (silu down to 3e-37, a normal bf16) times 1: every M takes another kernel.  __expf of
+    arguments to 88.5 is good to 2 ulps + 88.5 2^-23 relative from its scaled argument's rounding; with bf16's 2^-9 taken
+    twice 2^-7 covers both."""
+    N, K = 512, 128
+    A = torch.zeros(M, K, device="cuda", dtype=torch.bfloat16)
+    gate = -80 - torch.arange(M, device="cuda") % 18 * 0.5    # a bf16 each
+    A[:, 0] = gate.to(torch.bfloat16)
+    A[:, 1] = 1
+    W = torch.zeros(N, K, device="cuda", dtype=torch.bfloat16)
+    W[:N // 2, 0] = 1
+    W[N // 2:, 1] = 1
+    if w8:
+        got = B.eb_op_gemm_w8(A, W.float().to(torch.float8_e4m3fn).view(torch.uint8), torch.ones(N, device="cuda"),
+                              "silu_mul")
+    else:
+        got = B.eb_op_gemm(A, W, "silu_mul")
+    g = A[:, :1].double()
+    ref = (g * torch.sigmoid(g)).expand(M, N // 2)
+    assert ((got.double() - ref).abs() <= 2.0 ** -7 * ref.abs()).all()
+
+
+@pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
 @pytest.mark.parametrize("epi", ["store", "residual", "silu_mul"])
 @pytest.mark.parametrize("M,N,K", [(256, 528, 64), (257, 4112, 128), (511, 264, 192), (700, 2064, 4160)])
 def test_big_tiles(M, N, K, epi, w8):
