@@ -130,7 +130,9 @@ MoeBufs moe_bufs(const MoeArgs &a) {
   // on average the 256 x 256 kernel takes tiles of up to 256 rows (gate/up +
   // down on 128 experts of 768: 64 rows each 187 + 112 us streamed, 185 + 124
   // in 256 x 256 tiles; 125 rows each 242 + 154 against 202 + 140)
-  B.tile_rows = (long)a.T * a.k >= 80L * a.E && a.d % 64 == 0 && a.F % 64 == 0 ? 256 : 64;
+  // (a 256-row tile's outputs, fp32 [d] and bf16 [F], stay inside a 32-bit buffer range)
+  const bool fits = (size_t)256 * a.d * 4 < ((size_t)1 << 31) && (size_t)256 * a.F * 2 < ((size_t)1 << 31);
+  B.tile_rows = fits && (long)a.T * a.k >= 80L * a.E && a.d % 64 == 0 && a.F % 64 == 0 ? 256 : 64;
   return B;
 }
 hipError_t moe_products(const MoeBufs &B, const uint16_t *in, int in_rows, const int32_t *rows,

@@ -55,3 +55,29 @@ def test_moe_edges(d, E, k, F, T):
         bound.index_add_(0, t, wt * (me @ dw.abs().t() + (F + k) * 2.0 ** -23 * (m.abs() @ dw.abs().t())))
     err = (out.double() - ref).abs()
     assert (err <= 2.0 ** -8 * ref.abs() + bound + 1e-6).all(), (err - bound).max().item()
+
+
+def test_rows_wider_than_a_tiles_buffer_range():
+    """256 rows of one expert, 2^21 + 64 fp32 outputs each: more than the 2^31 bytes that one buffer range of the 256-row
+    tiles could address (columns outside the matrix, dropped by that range, landed inside it)."""
+    T, d, E, k, F = 256, (1 << 21) + 64, 16, 5, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    b = torch.empty(T, d, **bf).normal_(generator=g)
+    b[:, 0] = 1
+    router = torch.zeros(E, d, **bf)
+    router[:k, 0] = torch.arange(k, 0, -1) * 0.25   # every token: experts 0 .. 4
+    gu = torch.empty(E, 2 * F, d, **bf).normal_(std=d ** -0.5, generator=g)
+    dw = torch.empty(E, d, F, **bf).normal_(generator=g)
+    out, ids, wts = B.eb_op_moe_ffn(b, router, gu, dw, k, return_routing=True)
+    assert (ids == torch.arange(k, device="cuda")).all()
+    at = (1 << 29) - 255 * d      # the column of the 256th row that lies 2^31 bytes into the tile
+    cols = torch.cat([torch.arange(256), torch.arange(at - 128, at + 128), torch.arange(d - 256, d)]).cuda()
+    ref, x = torch.zeros(T, cols.numel(), dtype=torch.float64, device="cuda"), b.double()
+    for e in range(k):
+        gt, up = x @ gu[e, :F].double().t(), x @ gu[e, F:].double().t()
+        ref += wts[:, e, None].double() * ((gt * torch.sigmoid(gt) * up) @ dw[e, cols].double().t())
+    # m is rounded to bf16 (2^-9 of each of the 64 terms), the sums behind it to 1e-4 of values near 1
+    err = (out[:, cols].double() - ref).abs().max() / ref.abs().max()
+    assert err < 1e-2, err.item()
