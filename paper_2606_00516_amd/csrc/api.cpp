@@ -165,7 +165,7 @@ hipError_t moe_second(const MoeArgs &a, hipStream_t st) {
 struct WsLayout {
   size_t meta = 0, act = 0, qkv = 0, attn = 0, h1 = 0, mlp = 0, part_o = 0, part_ml = 0, gemm = 0, alt = 0,
          moe = 0, ssq = 0, total = 0;
-  size_t gemm_max = (size_t)-1;  // split-K partials of one projection stay within this (plan_gemm)
+  size_t gemm_max = (size_t)-1;  // plan_gemm's max_ws for every projection of the step
 };
 
 constexpr int kMaxStreamSplits = 8;  // of a projection whose row sums of squares go to WsLayout::ssq
@@ -187,8 +187,8 @@ WsLayout layout_for(const Shape &s, const HostPlan &p, bool full_step, bool stac
   };
   const size_t T = (size_t)p.T;
   L.meta = take(p.blob.size() * sizeof(int32_t));
-  L.part_o = take((size_t)p.total_splits * s.nkv * s.group() * s.hd * sizeof(float));
-  L.part_ml = take((size_t)p.total_splits * s.nkv * s.group() * 2 * sizeof(float));
+  const size_t meta_end = off;
+  size_t g = 0, ss_splits = 1;
   if (full_step) {
     L.act = take(T * s.hidden * 2);
     L.qkv = take(T * s.qkv_cols() * 2);
@@ -196,17 +196,20 @@ WsLayout layout_for(const Shape &s, const HostPlan &p, bool full_step, bool stac
     L.h1 = take(T * s.hidden * 2);
     if (!s.moe()) L.mlp = take(T * s.ffn * 2);
     if (s.moe()) L.moe = take(moe_layout(p.T, s.hidden, s.ne, s.topk, s.effn).total);
-    // Batches of 65 to 255 rows split K into as many parts as they have CUs to
-    // fill, as long as the step still fits the fixed scratch of the entry point
-    // without a workspace (a batch that fits it with no partials at all is
-    // never refused for them); the same plan with any workspace, so that both
-    // entry points give the same bits.
+    // Batches of more than 64 rows split K into as many parts as they have CUs
+    // to fill, as long as the step still fits the fixed scratch of the entry
+    // point without a workspace (or the entry could hold no such batch at
+    // all).  The limit follows from the rows and the shape alone, with the
+    // metadata at its largest: a row's bits and a step's time do not depend on
+    // the workspace that the caller brought, nor on the contexts of the batch
+    // (8B, 160 requests at 9800, when it shrank with them: K unsplit).
     const int M = p.T;
-    const size_t least = off + align_up(T * sizeof(float));  // unsplit
-    const size_t rest = off + align_up(kMaxStreamSplits * T * sizeof(float));
-    if (M > 64 && M < 256 && least <= kNoAllocScratchBytes)
-      L.gemm_max = rest <= kNoAllocScratchBytes ? kNoAllocScratchBytes - rest : 0;
-    size_t g = 0, ss_splits = 1;
+    const size_t fixed = off - meta_end;
+    if (M > 64 && fixed + align_up(T * sizeof(float)) <= kNoAllocScratchBytes) {
+      const size_t most = align_up(plan_capacity(M, M, s.group()) * sizeof(int32_t)) + fixed +
+                          align_up(kMaxStreamSplits * T * sizeof(float));
+      L.gemm_max = most <= kNoAllocScratchBytes ? kNoAllocScratchBytes - most : 0;
+    }
     // room for the plans of either weight type (the feed-forward ones when dense)
     for (int w8 = 0; w8 < 2; ++w8) {
       const int nplans = s.moe() ? 2 : 4;  // (an MoE layer has no dense feed-forward GEMMs)
@@ -220,8 +223,21 @@ WsLayout layout_for(const Shape &s, const HostPlan &p, bool full_step, bool stac
         if (i == 0 && fused_qkv(gp) && (size_t)gp.splits > ss_splits) ss_splits = gp.splits;
       }
     }
+  }
+  // The decode attention's partials live from its launch to the combine; the
+  // QKV projection's and the row sums of squares are consumed before it, the
+  // other projections' are written after it: one place serves both.  So
+  // longer contexts never need less, and the projections' share takes
+  // nothing from what they leave.
+  const size_t shared = off;
+  L.part_o = take((size_t)p.total_splits * s.nkv * s.group() * s.hd * sizeof(float));
+  L.part_ml = take((size_t)p.total_splits * s.nkv * s.group() * 2 * sizeof(float));
+  if (full_step) {
+    const size_t attn_end = off;
+    off = shared;
     L.gemm = take(g);
     L.ssq = take(ss_splits * T * sizeof(float));
+    off = std::max(off, attn_end);
     if (stack) L.alt = take(T * s.hidden * 2);
   }
   L.total = off;

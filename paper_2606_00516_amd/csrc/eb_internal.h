@@ -120,8 +120,8 @@ struct GemmPlan {
 };
 // w8: W holds 8-bit E4M3 codes with one fp32 scale per row (launch_gemm's
 // wscale, null for bf16 weights); such plans never take the tiled kernel.
-// max_ws: where the plan below 256 rows has no room for its partials there,
-// one that needs less is made.
+// max_ws: where the weight-streaming kernel's partials, or those of 256 x 256
+// tiles below 256 rows, have no room there, a plan that needs less is made.
 GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8 = false, size_t max_ws = (size_t)-1);
 // With nf, a residual GEMM whose plan splits K also writes the RMSNorm of
 // its result rows (gamma, out, eps) from the split-K sum and sets nf->done;
