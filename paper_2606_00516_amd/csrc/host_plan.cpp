@@ -260,10 +260,14 @@ void build_plan(const eb_layer_config &cfg, const eb_batch &b, eb_mode mode, Hos
     }
   }
   p.o_dec_info = put(info.data(), info.size());
-  std::vector<int32_t> part_d(parts.size());
+  // the requests with a shorter last split, then the short ones: one entry per
+  // decode request kept for both, so that the size does not depend on how many
+  // contexts fill their last split
+  std::vector<int32_t> part_d(dec_seq.size());
   for (size_t j = 0; j < parts.size(); ++j) part_d[j] = parts[j].d;
+  std::copy(shorts.begin(), shorts.end(), part_d.begin() + parts.size());
   p.o_part = put(part_d.data(), part_d.size());
-  p.o_short = put(shorts.data(), shorts.size());
+  p.o_short = p.o_part + parts.size();
   std::vector<int32_t> comb_rec((size_t)kCombInfo * comb.size(), 0);
   for (size_t j = 0; j < comb.size(); ++j) {
     const int d = comb[j];

@@ -185,11 +185,12 @@ def test_wide_decode_batch_fits_the_fixed_scratch(T, ctx):
 @pytest.mark.parametrize("shape", [gen.L8B, gen.L70B, gen.Q30B], ids=lambda s: s.name)
 @pytest.mark.parametrize("T", [1, 64, 65, 100, 128, 160, 192, 252, 256, 300])
 def test_workspace_never_falls_with_contexts(shape, T):
-    """A workspace sized for a batch's longest contexts serves every shorter one of as many rows.  (Host planning alone;
-    contexts that fill a last split, whose requests need one metadata entry less, are not among them.)"""
+    """A workspace sized for a batch's longest contexts serves every shorter one of as many rows (host planning alone).
+    Among the contexts: those around 64 keys, from which on a request is split, and around whole 512-key splits."""
     h = B.Handle(shape, T, T)
     one = np.ones(T, np.int32)
-    sizes = [B.eb_workspace_bytes(h, np.full(T, c, np.int32), one, "decode") for c in range(70, 16400, 300)]
+    ctx = sorted({*range(0, 16400, 300), *(s - 1 + d for s in (64, *range(512, 16385, 512)) for d in (-1, 0, 1))})
+    sizes = [B.eb_workspace_bytes(h, np.full(T, c, np.int32), one, "decode") for c in ctx]
     assert sizes == sorted(sizes), [(a, b) for a, b in zip(sizes, sizes[1:]) if b < a]
 
 
