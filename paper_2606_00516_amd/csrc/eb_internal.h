@@ -154,10 +154,10 @@ hipError_t launch_gemm_prenorm(const GemmPlan &p, const uint16_t *x, const uint1
 // *n_tiles of them in use) by their expert's W ([E][N][K] bf16), gathering A
 // rows through a_rows (null: the sorted row itself); SiLU epilogue to bf16
 // [rows, N / 2], or store to fp32 [rows, N] when f32_out.  Tiles of up to
-// 64 rows.
+// 64 rows; once: most experts have one, so W by non-temporal loads.
 hipError_t launch_gemm_grouped(const uint16_t *A, int a_nrows, const int32_t *a_rows, const uint16_t *W, void *out,
                                bool f32_out, const int32_t *tiles, const int32_t *n_tiles, int max_tiles, int N, int K,
-                               int epi, hipStream_t st);
+                               int epi, bool once, hipStream_t st);
 // The same on the 256 x 256 kernel: tiles of up to 256 rows, K a multiple of 64.
 hipError_t launch_gemm_grouped_big(const uint16_t *A, int a_nrows, const int32_t *a_rows, const uint16_t *W,
                                    void *out, bool f32_out, const int32_t *tiles, const int32_t *n_tiles, int max_tiles,

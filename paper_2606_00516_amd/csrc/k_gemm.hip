@@ -63,6 +63,13 @@ __device__ __forceinline__ void dma_lds16(u32x4_t rsrc, uint32_t voff, uint32_t 
                : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
                : "memory", "m0");
 }
+// The same for data that nothing reads again (non-temporal).
+__device__ __forceinline__ void dma_lds16_once(u32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory", "m0");
+}
 // The same with 4 bytes per lane (256 bytes per instruction).
 __device__ __forceinline__ void dma_lds4(u32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
@@ -466,7 +473,7 @@ struct StreamTraits {
   static_assert(LA * NW * 1024 == A_BYTES && LW * NW * 1024 == W_BYTES && NI * WM * 16 == BM, "wave shares");
 };
 
-template <int BM, bool W8, bool PRENORM, bool GROUPED = false>
+template <int BM, bool W8, bool PRENORM, bool GROUPED = false, bool ONCE = false>
 __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) void k_gemm_stream(
     const uint16_t *__restrict__ A, const void *__restrict__ W, const float *__restrict__ wscale,
     uint16_t *__restrict__ out, const uint16_t *__restrict__ res, float *__restrict__ part, int M, int N, int K, int epi,
@@ -543,6 +550,7 @@ __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) 
   const u32x4_t ra = raw_rsrc(A, a_bytes), rw = raw_rsrc(W, w_bytes);
   const u32x4_t rg = raw_rsrc(PRENORM ? gamma : A, PRENORM ? (uint32_t)K * 2u : 0u);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)st_lds;
+  constexpr auto dma_w = ONCE ? dma_lds16_once : dma_lds16;
   // stage s into the ring slot at byte `slot`
   const int rot = gridDim.y == 1 ? k_start(ct, nct, (kend - kbeg + 127) / 128) * (128 / KC) : 0;
   auto issue = [&](int s, uint32_t slot) {
@@ -559,7 +567,7 @@ __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) 
 #pragma unroll
       for (int i = 0; i < LA; ++i) dma_lds16(ra, aoff[i], (uint32_t)k0 * 2u, da + i * 1024);
 #pragma unroll
-      for (int i = 0; i < LW; ++i) dma_lds16(rw, woff[i], (uint32_t)k0 * WES, dw + i * 1024);
+      for (int i = 0; i < LW; ++i) dma_w(rw, woff[i], (uint32_t)k0 * WES, dw + i * 1024);
     } else {  // the last stage of a ragged range, or past it (8-bit W: see clear_tail)
 #pragma unroll
       for (int i = 0; i < LA; ++i)
@@ -567,8 +575,8 @@ __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) 
                   da + i * 1024);
 #pragma unroll
       for (int i = 0; i < LW; ++i)
-        dma_lds16(rw, k0 + wchunk(i) * CK < kend && woff[i] != 0x80000000u ? woff[i] + (uint32_t)k0 * WES : 0x80000000u,
-                  0u, dw + i * 1024);
+        dma_w(rw, k0 + wchunk(i) * CK < kend && woff[i] != 0x80000000u ? woff[i] + (uint32_t)k0 * WES : 0x80000000u, 0u,
+              dw + i * 1024);
     }
   };
 
@@ -1435,6 +1443,17 @@ static void launch_big(dim3 grid, hipStream_t st, const uint16_t *A, const void 
                      per_xcd, kt_per, ga);
 }
 
+// W by non-temporal loads: with one block row (mt) every byte of W is used
+// once and only takes cache from the activations and partials.  70B gate/up
+// (940 MB) at one row 157 -> 144 us, 8B gate/up (235 MB) at 64 rows 43.8 ->
+// 40.0, of 8-bit codes 29.7 -> 28.0.  To 32 rows for every W larger than one
+// XCD's L2; above, where activations and partials weigh more, from 96 MiB (8B
+// qkv, 50 MB, at 64 rows 15.6 -> 17.4 with them, 8B down, 117 MB, 31.0 -> 28.8).
+static bool w_read_once(int mt, int M, int N, int K, bool w8) {
+  const size_t bytes = (size_t)N * K * (w8 ? 1 : 2);
+  return mt == 1 && bytes > (M <= 32 ? (size_t)4 << 20 : (size_t)96 << 20);
+}
+
 template <bool PRENORM>
 static hipError_t launch_stream(const uint16_t *A, const void *W, const float *wscale, uint16_t *out,
                                 const uint16_t *res, float *part, int M, int N, int K, int epi, int splits, int bm,
@@ -1447,9 +1466,11 @@ static hipError_t launch_stream(const uint16_t *A, const void *W, const float *w
   const int tiles = ((ncols + ST_BN - 1) / ST_BN) * mt;
   const int per_xcd = (tiles + 7) / 8;
   const dim3 grid(8 * per_xcd, splits);
+  const bool once = w_read_once(mt, M, N, K, w8);
 #define EB_STREAM(BM_, W8_)                                                                                         \
-  hipLaunchKernelGGL((k_gemm_stream<BM_, W8_, PRENORM>), grid, dim3(64 * StreamTraits<BM_, W8_, PRENORM>::NW),       \
-                     (StreamTraits<BM_, W8_, PRENORM>::LDS), st, A, W, wscale, out, res, part, M, N, K, epi, per, tiles, mt, per_xcd, gamma, ssq)
+  hipLaunchKernelGGL((once ? k_gemm_stream<BM_, W8_, PRENORM, false, true> : k_gemm_stream<BM_, W8_, PRENORM>), grid, \
+                     dim3(64 * StreamTraits<BM_, W8_, PRENORM>::NW), (StreamTraits<BM_, W8_, PRENORM>::LDS), st, A, W, \
+                     wscale, out, res, part, M, N, K, epi, per, tiles, mt, per_xcd, gamma, ssq, GroupedArgs{})
   if (w8) {
     if (bm == 64)
       EB_STREAM(64, true);
@@ -1569,16 +1590,16 @@ hipError_t launch_gemm_grouped_big(const uint16_t *A, int a_nrows, const int32_t
 
 hipError_t launch_gemm_grouped(const uint16_t *A, int a_nrows, const int32_t *a_rows, const uint16_t *W, void *out,
                                bool f32_out, const int32_t *tiles, const int32_t *n_tiles, int max_tiles, int N, int K,
-                               int epi, hipStream_t st) {
+                               int epi, bool once, hipStream_t st) {
   if (max_tiles <= 0) return hipSuccess;
   const int nct = (logical_cols(N, epi) + ST_BN - 1) / ST_BN;
   const unsigned grid = ((unsigned)max_tiles * (unsigned)nct + 7) / 8 * 8;
   const GroupedArgs ga{a_rows, tiles, n_tiles, max_tiles, a_nrows, f32_out ? 1 : 0};
   uint16_t *o16 = f32_out ? nullptr : static_cast<uint16_t *>(out);
   float *o32 = f32_out ? static_cast<float *>(out) : nullptr;
-  hipLaunchKernelGGL((k_gemm_stream<64, false, false, true>), dim3(grid), dim3(256),
-                     (StreamTraits<64, false, false, true>::LDS), st, A, W, nullptr, o16, nullptr, o32, 0, N, K, epi,
-                     (K + 31) / 32, 0, nct, 0, nullptr, nullptr, ga);
+  hipLaunchKernelGGL((once ? k_gemm_stream<64, false, false, true, true> : k_gemm_stream<64, false, false, true>),
+                     dim3(grid), dim3(256), (StreamTraits<64, false, false, true>::LDS), st, A, W, nullptr, o16, nullptr,
+                     o32, 0, N, K, epi, (K + 31) / 32, 0, nct, 0, nullptr, nullptr, ga);
   return hipGetLastError();
 }
 

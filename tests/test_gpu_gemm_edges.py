@@ -76,6 +76,14 @@ def test_nan_codes_stay_in_their_row(M, N, K):
     assert torch.equal(got[:, ~bad], clean[:, ~bad])
 
 
+@pytest.mark.parametrize("M,N,K,w8", [(32, 4104, 1032, False), (33, 4104, 1032, False), (32, 8208, 1032, True),
+                                      (64, 24584, 2056, False), (65, 24584, 2056, False), (130, 24584, 2056, False),
+                                      (200, 24584, 2056, False), (64, 49160, 2056, True), (65, 49160, 2056, True)])
+def test_stream_once(M, N, K, w8):
+    """Both sides of the sizes from which W is loaded past the caches (4 MiB to 32 rows, 96 MiB above)."""
+    _check(M, N, K, "residual", w8)
+
+
 @pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
 @pytest.mark.parametrize("M,N,K", [(33, 28688, 512), (100, 28688, 512), (180, 28688, 264), (240, 28688, 1152),
                                    (64, 25600, 136), (130, 1376, 256)])
