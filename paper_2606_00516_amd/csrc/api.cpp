@@ -130,10 +130,14 @@ MoeBufs moe_bufs(const MoeArgs &a) {
   // tiles of 64 rows (tiles of 32 measured the same); from 80 rows per expert
   // on average the 256 x 256 kernel takes tiles of up to 256 rows (gate/up +
   // down on 128 experts of 768: 64 rows each 187 + 112 us streamed, 185 + 124
-  // in 256 x 256 tiles; 125 rows each 242 + 154 against 202 + 140)
+  // in 256 x 256 tiles; 125 rows each 242 + 154 against 202 + 140), unless the
+  // block has so little work that the start and end of a large tile are most
+  // of it (blocks of 16 experts of 128 over 256: 128 rows each 25 us streamed,
+  // 37 in 256 x 256 tiles; 1024 rows each 48 against 55, 2048 62 against 60)
   // (a 256-row tile's outputs, fp32 [d] and bf16 [F], stay inside a 32-bit buffer range)
   const bool fits = (size_t)256 * a.d * 4 < ((size_t)1 << 31) && (size_t)256 * a.F * 2 < ((size_t)1 << 31);
-  B.tile_rows = fits && (long)a.T * a.k >= 80L * a.E && a.d % 64 == 0 && a.F % 64 == 0 ? 256 : 64;
+  const bool work = (size_t)a.T * a.k * a.d * a.F >= (size_t)1 << 30;
+  B.tile_rows = fits && work && (long)a.T * a.k >= 80L * a.E && a.d % 64 == 0 && a.F % 64 == 0 ? 256 : 64;
   // non-temporal weight loads while an expert has one row tile and not two (64
   // tokens of 128 experts of 768: block 227 -> 196 us, 512 tokens 254 -> 235;
   // 1024 tokens, 64 rows each, 317 -> 338)

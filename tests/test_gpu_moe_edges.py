@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
     (256, 16, 4, 128, 1), (256, 16, 4, 128, 1023), (256, 16, 4, 128, 1024), (256, 16, 4, 128, 2049),
     (96, 256, 6, 40, 2100),      # two logits column tiles, K ends inside a stage, 64-row tiles
     (96, 256, 6, 40, 700),       # the plan on several blocks, few rows per expert
-    (128, 32, 3, 64, 1500),      # 256-row tiles of a single K tile down
+    (128, 32, 3, 64, 1500),      # many rows per expert, too little work for 256-row tiles
+    (512, 16, 4, 576, 1000), (512, 16, 4, 512, 1023), (512, 16, 4, 512, 1024),   # 256-row tiles; both sides of 2^30
+    (4096, 16, 8, 64, 520),      # 256-row tiles of a single K tile down
     (2080, 48, 5, 24, 70), (64, 16, 16, 8, 300)])
 def test_moe_edges(d, E, k, F, T):
     shape = gen.MoeShape("edge", d, E, k, F)
