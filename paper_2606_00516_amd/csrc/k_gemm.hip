@@ -16,6 +16,8 @@
 // processed in groups of 64 = 32 gate rows of W followed by the 32 matching
 // up rows (gate rows 0..F-1, up rows F..2F-1 of W), so that every lane holds
 // a gate accumulator and its up partner.
+#include <algorithm>
+
 #include "device_common.h"
 #include "eb_internal.h"
 
@@ -423,7 +425,7 @@ struct GroupedArgs {
 // to 64 rows) in flight across the one barrier a stage has.  The kernel before
 // it staged through registers, two 128-wide stages ahead, and drained at each
 // barrier: 64 rows, qkv 22.3 -> 17.8 us, gate/up 51.2 -> 43.3; 8-bit W at 37
-// rows, gate/up 41.0 -> 28.1, down 24.7 -> 20.4; more rows: stream_bm.
+// rows, gate/up 41.0 -> 28.1, down 24.7 -> 20.4; more rows: stream_us.
 //
 // Eight waves, two on each SIMD, so that one issues loads or waits while the
 // other multiplies (four waves, one a SIMD, before: 8-bit W at 37 rows, gate/up
@@ -1208,9 +1210,6 @@ __global__ __launch_bounds__(BG_THREADS) void k_gemm_big(const uint16_t *__restr
 // ===========================================================================
 // planning and launch
 // ===========================================================================
-// Row counts up to this use the weight-streaming kernels.
-constexpr int kStreamMaxRows = 256;
-
 // The split-K sum of a residual GEMM and the RMSNorm of its rows in one
 // pass: h = bf16(sum_s part[s] + res) is stored (the splits summed in order,
 // as the split-K epilogue does), then out = bf16(h * inv * g) with inv from
@@ -1320,18 +1319,6 @@ static hipError_t finish_splitk(const float *part, int splits, uint16_t *out, co
   return launch_splitk_epilogue(part, splits, out, res, M, N, epi, st);
 }
 
-// Rows per block of the stream kernel: all of the batch, so that W goes to a
-// CU once (160 rows: gate/up 109 -> 62 us, o 32 -> 22, down 64 -> 39 against
-// three blocks of 64 rows); 8-bit W stops at 128 rows, where its ring is three
-// stages deep.  A W that fits one XCD's L2 (4 MiB) costs nothing to read
-// again, and then more, smaller blocks have the shorter chain (the tiny
-// layer's four products: 47 us at 192 rows per block against 34 at 64).
-static int stream_bm(int M, int N, int K, bool w8) {
-  if (M <= 64 || (size_t)N * K * (w8 ? 1 : 2) <= ((size_t)4 << 20)) return 64;
-  if (M <= 128 || w8) return 128;
-  return M <= 192 ? 192 : 256;
-}
-
 constexpr int kMaxSplits = 8;
 static int stream_splits(int M, int N, int K, int bm) {
   const int tiles = ((N + ST_BN - 1) / ST_BN) * ((M + bm - 1) / bm);
@@ -1350,36 +1337,71 @@ static int stream_splits(int M, int N, int K, int bm) {
   return best;
 }
 
-// 129 to 255 rows: both kernels read W once.  The 256 x 256 tiles (padded to
-// 256 rows) are the faster ones where they fill 3/4 of the CUs unsplit (70B
-// gate/up at 200 rows: 205 us against 267), where both kernels split a long K
-// over many columns (70B down 127 against 143, qkv 57 against 63, o 52 both),
-// and for 8-bit W, which the stream kernel would read twice (8B gate/up 63
-// against 78, qkv 33 against 43, down 47 against 45; 70B 194 against 277).  The stream
-// kernel is where its 128 columns a block need no split and 256 would (8B
-// gate/up at 160 / 240 rows: 58 / 71 against 75 / 83), and on the narrower
-// split products (8B down at 200 rows 44 against 53, qkv 28 against 33).
-static bool big_below_256(int M, int ncols, int K, bool w8) {
-  if (M <= 128 || M >= 256) return false;
-  if (w8 || (ncols + BG_BN - 1) / BG_BN >= 192) return true;
-  return (ncols + ST_BN - 1) / ST_BN < 192 && ncols >= 8192 && K >= 8192;
+// What a plan takes, in microseconds, less what all plans share: rounds of 256
+// blocks (one per CU), each a start and its K stages, or W's way from HBM
+// where that is longer, and for a split K the sum's launch and the fp32
+// partials written and read.  More rows per block mean fewer bytes of W
+// through a CU's LDS, fewer mean more blocks at work and less K to split, and
+// which of them decides depends on how the blocks fill their rounds, so the
+// plans are compared by these estimates.  Their constants are fitted to every
+// choice timed at 65 to 256 rows of 17 products (K 256 to 28672, N 256 to
+// 57344, 0.1 MB to 0.9 GB) of both weight types: the plan chosen is within
+// 1.3 % (8-bit W 0.6 %) of the fastest of them on average, 20 % at worst (rows
+// that are no whole cache lines).  The lines drawn through a few 8B and 70B
+// shapes before had 8-bit W on 256 x 256 tiles from 129 rows on (a W of 0.1 MB
+// at 200 rows: 20.5 us, now 6; 8B qkv at 255 rows 38, now 26), and as few
+// blocks as possible elsewhere (2048 x 2048 at 255 rows 24, now 17; 8208 x
+// 1048 at 192 rows 26, now 15; 8B gate/up at 160 rows 60 us then and now).
+static float split_us(int splits, int M, int ncols) {
+  return splits > 1 ? 4.f + (float)splits * (float)M * (float)ncols * (8.f / 6e6f) : 0.f;
+}
+static float w_us(int N, int K, bool w8, bool once) {
+  return (float)N * (float)K * (w8 ? 1.f : 2.f) / (once ? 5.5e6f : 4.5e6f);
+}
+static float stream_us(int M, int N, int K, int ncols, bool w8, int bm, int splits) {
+  const int mt = (M + bm - 1) / bm, tiles = (ncols + ST_BN - 1) / ST_BN * mt;
+  const int rounds = (tiles * splits + 255) / 256;
+  const int range = ((K + 31) / 32 + splits - 1) / splits * 32, stages = (range + (w8 ? 127 : 63)) / (w8 ? 128 : 64);
+  float stage = w8 ? (bm == 64 ? 0.65f : 1.08f) : bm == 64 ? 0.45f : bm == 128 ? 0.65f : bm == 192 ? 0.83f : 0.97f;
+  // a 128-byte run of a row that is no whole number of cache lines touches two
+  // of them: more so, the more rows of A a block loads
+  if (!w8 && bm > 64 && K % 64) stage *= 1.6f;
+  const float blocks = (float)rounds * ((w8 ? 3.2f : 2.f) + (float)stages * stage);
+  return std::max(blocks, w_us(N, K, w8, mt == 1)) + split_us(splits, M, ncols);
+}
+static float big_us(int M, int N, int K, int ncols, bool w8, const GemmPlan &p) {
+  const long tiles = (long)((M + BG_BM - 1) / BG_BM) * ((ncols + BG_BN - 1) / BG_BN);
+  const float blocks = (float)((tiles * p.splits + 255) / 256) * ((w8 ? 7.f : 4.f) + (float)p.kt_per * (w8 ? 1.3f : 1.5f));
+  return std::max(blocks, w_us(N, K, w8, true)) + split_us(p.splits, M, ncols);
 }
 
 GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8, size_t max_ws) {
-  GemmPlan p{};
-  p.splits = 1;
-  if (M <= 0 || N <= 0 || K <= 0) return p;  // nothing to plan (kind 0, no workspace)
+  GemmPlan none{};
+  none.splits = 1;
+  if (M <= 0 || N <= 0 || K <= 0) return none;  // nothing to plan (kind 0, no workspace)
   const int ncols = logical_cols(N, epi);
+  const size_t one = (size_t)M * ncols * sizeof(float);  // the partials of one split
   // the big kernel addresses W through a 32-bit buffer range; A is cut into
   // row chunks that each fit one (launch_gemm)
   // (and a tile's rows of the output through another)
-  const bool fits = (size_t)N * K * 2 < ((size_t)1 << 31) && (size_t)BG_BM * K * 2 < ((size_t)1 << 31) &&
-                    (size_t)BG_BM * ncols * 4 < ((size_t)1 << 31);
-  // 256 x 256 tiles once the grid covers at least half the CUs
-  const long big_tiles = (long)((M + BG_BM - 1) / BG_BM) * ((ncols + BG_BN - 1) / BG_BN);
-  if (K % BG_BK == 0 && N % 8 == 0 && fits && (M >= 256 || big_below_256(M, ncols, K, w8))) {
+  const bool big_fits = K % BG_BK == 0 && N % 8 == 0 && (size_t)N * K * 2 < ((size_t)1 << 31) &&
+                        (size_t)BG_BM * K * 2 < ((size_t)1 << 31) && (size_t)BG_BM * ncols * 4 < ((size_t)1 << 31);
+  // the weight-streaming kernels address both operands through 32-bit buffer ranges
+  const bool stream_fits = (size_t)N * K * (w8 ? 1 : 2) < ((size_t)1 << 31) && (size_t)M * K * 2 < ((size_t)1 << 31);
+  // A W that one XCD's L2 holds costs nothing to read again, and many small
+  // blocks have the shorter chain at any number of rows (256 x 256 at 512
+  // rows: 21 us in 256 x 256 tiles, 5.6 in blocks of 64 rows)
+  const bool small_w = (size_t)N * K * (w8 ? 1 : 2) <= ((size_t)4 << 20);
+  // (the tiled kernel, for what the others do not take, reads bf16 weights only)
+  const bool stream = stream_fits && (M < BG_BM || small_w || (!big_fits && (M == BG_BM || w8)));
+  GemmPlan best = none;
+  best.kind = w8 ? -1 : 1;  // -1: no kernel here addresses 8-bit operands this large
+  float best_us = 0.f;
+  if (big_fits && (M >= BG_BM || (M > 128 && stream))) {
     // one block per CU: split K while the tiles cover at most half the CUs,
     // keeping at least 8 K tiles per split
+    const long big_tiles = (long)((M + BG_BM - 1) / BG_BM) * ((ncols + BG_BN - 1) / BG_BN);
+    GemmPlan p = none;
     p.kind = 2;
     const int nk = K / BG_BK;
     int splits = 1;
@@ -1388,30 +1410,32 @@ GemmPlan plan_gemm(int M, int N, int K, int epi, bool w8, size_t max_ws) {
       splits = (int)(by_cus < by_k ? by_cus : by_k);
     }
     if (splits < 1) splits = 1;
+    // (the scratch's limit binds only where the other kernels are a choice)
+    while (stream && splits > 1 && splits * one > max_ws) --splits;
     p.kt_per = (nk + splits - 1) / splits;
     p.splits = (nk + p.kt_per - 1) / p.kt_per;
-    p.ws_bytes = p.splits > 1 ? (size_t)p.splits * M * ncols * sizeof(float) : 0;
-    if (M >= 256 || p.ws_bytes <= max_ws) return p;
+    p.ws_bytes = p.splits > 1 ? p.splits * one : 0;
+    if (!stream) return p;
+    best = p;
+    best_us = big_us(M, N, K, ncols, w8, p);
   }
-  // the weight-streaming kernels address both operands through 32-bit buffer ranges
-  const bool sk_fits = (size_t)N * K * (w8 ? 1 : 2) < ((size_t)1 << 31) && (size_t)M * K * 2 < ((size_t)1 << 31);
-  if ((M <= kStreamMaxRows || w8) && sk_fits) {  // (the tiled kernel reads bf16 weights only)
-    p.kind = 0;
-    p.bm = stream_bm(M, N, K, w8);
-    p.splits = stream_splits(M, ncols, K, p.bm);
-    const size_t one = (size_t)M * ncols * sizeof(float);
-    if (p.splits > 1 && p.splits * one > max_ws) {  // no room: blocks of 64 rows need fewer splits
-      p.bm = 64;
-      p.splits = stream_splits(M, ncols, K, 64);
-      while (p.splits > 1 && p.splits * one > max_ws) --p.splits;
+  if (!stream) return best;
+  // up to 64 rows one block row holds the batch; above, the rows per block
+  // (to the batch's own; 8-bit W stops at 128, where its ring is three stages
+  // deep) with the least time, each with the splits that there is room for
+  for (int bm = 64; bm <= (w8 ? 128 : 256) && (bm == 64 || bm - 64 < M); bm += 64) {
+    GemmPlan p = none;
+    p.bm = bm;
+    p.splits = stream_splits(M, ncols, K, bm);
+    while (p.splits > 1 && p.splits * one > max_ws) --p.splits;
+    p.ws_bytes = p.splits > 1 ? p.splits * one : 0;
+    const float us = stream_us(M, N, K, ncols, w8, bm, p.splits);
+    if (best.kind == 1 || best.kind == -1 || us < best_us) {
+      best = p;
+      best_us = us;
     }
-    p.ws_bytes = p.splits > 1 ? (size_t)p.splits * M * ncols * sizeof(float) : 0;
-    return p;
   }
-  p.kind = w8 ? -1 : 1;  // -1: no kernel here addresses 8-bit operands this large
-  p.splits = 1;
-  p.ws_bytes = 0;
-  return p;
+  return best;
 }
 
 bool packed_ok(int N, int K, int epi) {

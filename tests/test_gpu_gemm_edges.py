@@ -93,6 +93,19 @@ def test_stream_silu(M, N, K, w8):
 
 
 @pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
+@pytest.mark.parametrize("M,N,K,epi", [
+    (255, 2056, 2048, "residual"), (130, 2056, 2048, "store"),   # four and three block rows of 64, split
+    (96, 28672, 512, "silu_mul"), (160, 6144, 4096, "residual"), (135, 24584, 1024, "store"),     # 128, 192 rows
+    (224, 28672, 1024, "silu_mul"), (250, 6144, 4096, "store"), (250, 12296, 4096, "residual"),   # 256 rows; 2 x 128
+    (200, 57344, 512, "silu_mul"), (130, 8200, 8192, "residual"), (180, 8200, 16384, "store"),    # part of a 256 x 256
+    (150, 4104, 16384, "residual"),                              # tile, unsplit and split
+    (256, 264, 520, "store"), (700, 264, 520, "residual"), (3000, 264, 264, "silu_mul")])         # a W inside one L2
+def test_plans_by_time(M, N, K, epi, w8):
+    """One shape or more for each kernel and block size that the estimated times choose between."""
+    _check(M, N, K, epi, w8)
+
+
+@pytest.mark.parametrize("w8", [False, True], ids=["bf16", "w8"])
 @pytest.mark.parametrize("M", [40, 100, 300])
 def test_silu_at_the_end_of_its_range(M, w8):
     """Gates from -88.5 to -80 (silu down to 3e-37, a normal bf16) times 1: every M takes another kernel.  __expf of
@@ -124,9 +137,10 @@ def test_big_tiles(M, N, K, epi, w8):
 
 
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "w8"])
-@pytest.mark.parametrize("T", [65, 130, 200])
+@pytest.mark.parametrize("T", [64, 65, 130, 200])
 def test_layer_rows(T, fp8):
-    """Decode layers of more than 64 rows whose QKV projection takes the first RMSNorm with it, against the oracle."""
+    """Decode layers around 64 rows, to which the split QKV projection takes the first RMSNorm with it, and of more,
+    where the norm is a launch of its own, against the oracle."""
     shape = gen.LayerShape("mid", 2048, 16, 4, 128, 2064, 1e4)
     rng = np.random.default_rng(T)
     case = make_case(shape, gen.batch_decode(T, 1, 40, rng),
@@ -168,11 +182,13 @@ def test_infinite_gain_stays_in_its_k_range(T, fp8):
         assert torch.isinf(new).all(), (k, torch.isnan(new).sum().item())
 
 
-@pytest.mark.parametrize("T,ctx", [(129, 500), (252, 100), (252, 500), (252, 900)])
-def test_wide_decode_batch_fits_the_fixed_scratch(T, ctx):
+@pytest.mark.parametrize("shape,T,ctx", [(gen.L8B, 129, 500), (gen.L8B, 252, 100), (gen.L8B, 252, 500),
+                                         (gen.L8B, 252, 900), (gen.L70B, 200, 200), (gen.L70B, 252, 600)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_wide_decode_batch_fits_the_fixed_scratch(shape, T, ctx):
     """Batches of 129 to 255 rows split K further than their 64-row blocks would, but never out of the scratch of the
-    entry point without a workspace: what fits it without partials still does, with the bits of the regular step."""
-    shape = gen.L8B
+    entry point without a workspace (the 70B shape's are cut to it): what fits it without partials still does, with the
+    bits of the regular step."""
     rng = np.random.default_rng(T + ctx)
     batch = gen.batch_decode(T, ctx - 50, ctx, rng)
     w = gen.make_weights(shape, device="cuda")
