@@ -177,12 +177,14 @@ struct WsLayout {
   size_t gemm_max = (size_t)-1;  // plan_gemm's max_ws for every projection of the step
 };
 
-constexpr int kMaxStreamSplits = 8;  // of a projection whose row sums of squares go to WsLayout::ssq
-
 // A decode-sized QKV projection (weight streaming with split K) takes the
 // first RMSNorm into its operand staging and its split-K sum into the RoPE /
-// append kernel: two launches fewer per layer.
-bool fused_qkv(const GemmPlan &qp) { return qp.kind == 0 && qp.splits >= 2; }
+// append kernel: two launches fewer per layer.  To 64 rows (8B, 64 rows: step
+// 123.3 -> 118.9 us); with more, every column tile's block normalising all rows
+// again costs more than the launches (128 rows: 8B 152 against 151 us, 70B 405
+// against 406, of 8-bit weights 315 against 328; 160 rows: 174 against 177 and
+// 444 against 456; 252 rows: 210 against 216 and 522 against 559).
+bool fused_qkv(const GemmPlan &qp, int T) { return qp.kind == 0 && qp.splits >= 2 && T <= 64; }
 
 // full_step: buffers of a whole layer; stack: plus the second activation
 // buffer that consecutive layers of a stack alternate with y.
@@ -216,7 +218,7 @@ WsLayout layout_for(const Shape &s, const HostPlan &p, bool full_step, bool stac
     const size_t fixed = off - meta_end;
     if (M > 64 && fixed + align_up(T * sizeof(float)) <= kNoAllocScratchBytes) {
       const size_t most = align_up(plan_capacity(M, M, s.group()) * sizeof(int32_t)) + fixed +
-                          align_up(kMaxStreamSplits * T * sizeof(float));
+                          align_up(T * sizeof(float));
       L.gemm_max = most <= kNoAllocScratchBytes ? kNoAllocScratchBytes - most : 0;
     }
     // room for the plans of either weight type (the feed-forward ones when dense)
@@ -229,7 +231,7 @@ WsLayout layout_for(const Shape &s, const HostPlan &p, bool full_step, bool stac
                                      : plan_gemm(M, s.hidden, s.ffn, EPI_RESIDUAL, w8, L.gemm_max);
         g = gp.ws_bytes > g ? gp.ws_bytes : g;
         // row sums of squares of the fused first RMSNorm (either weight type)
-        if (i == 0 && fused_qkv(gp) && (size_t)gp.splits > ss_splits) ss_splits = gp.splits;
+        if (i == 0 && fused_qkv(gp, M) && (size_t)gp.splits > ss_splits) ss_splits = gp.splits;
       }
     }
   }
@@ -479,7 +481,7 @@ eb_status layer_body(eb_handle *h, const eb_layer_weights *w, const KV &kvd, con
   const GemmPlan qp = plan_gemm(T, sh.qkv_cols(), sh.hidden, EPI_STORE, w8, gemm_max);
   const uint16_t *g1 = static_cast<const uint16_t *>(w->attn_norm);
   const uint16_t *gq = static_cast<const uint16_t *>(w->q_norm), *gk = static_cast<const uint16_t *>(w->k_norm);
-  if (fused_qkv(qp)) {
+  if (fused_qkv(qp, T)) {
     // the first RMSNorm rides in the projection, the split-K sum in the RoPE
     // kernel (stage 0 stays empty)
     EB_STAGE(0, hipSuccess, "rmsnorm1");

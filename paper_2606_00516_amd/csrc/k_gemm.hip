@@ -1495,13 +1495,17 @@ static hipError_t launch_stream(const uint16_t *A, const void *W, const float *w
   hipLaunchKernelGGL((once ? k_gemm_stream<BM_, W8_, PRENORM, false, true> : k_gemm_stream<BM_, W8_, PRENORM>), grid, \
                      dim3(64 * StreamTraits<BM_, W8_, PRENORM>::NW), (StreamTraits<BM_, W8_, PRENORM>::LDS), st, A, W, \
                      wscale, out, res, part, M, N, K, epi, per, tiles, mt, per_xcd, gamma, ssq, GroupedArgs{})
-  if (w8) {
-    if (bm == 64)
+  if (bm == 64) {
+    if (w8)
       EB_STREAM(64, true);
     else
-      EB_STREAM(128, true);
-  } else if (bm == 64) {
-    EB_STREAM(64, false);
+      EB_STREAM(64, false);
+    return hipGetLastError();
+  }
+  if constexpr (PRENORM) {
+    return hipErrorInvalidValue;
+  } else if (w8) {
+    EB_STREAM(128, true);
   } else if (bm == 128) {
     EB_STREAM(128, false);
   } else if (bm == 192) {
