@@ -264,8 +264,14 @@ hipError_t launch_moe_route(const uint16_t *b, const uint16_t *wr, int T, int d,
                             float *logits, int32_t *ids, float *wts, hipStream_t st) {
   if (T <= 0) return hipSuccess;
   hipError_t e;
-  // (1024 tokens 10 us against 18 streamed, 3000 tokens 31 against 22, 8192 67 against 20)
-  if (T > 2048) {
+  // The wavefronts read every token row once per 16 experts, the streaming
+  // GEMM once per 128, in fewer and larger blocks: the line lies where T E
+  // reaches 2^18 (whole blocks of experts 8 wide and top 1, us, wavefronts
+  // against streamed, d 2048: 16 experts 8192 tokens 79 / 83, 16384 125 / 123;
+  // 64 experts 3000 59 / 63, 4096 68 / 69, 8192 100 / 85; 128 experts 1536 57 /
+  // 59, 2100 67 / 63; 256 experts 1024 69 / 68, 1536 79 / 70; d 512 and 4096
+  // cross within a factor of 1.5 of it)
+  if ((size_t)T * E > (size_t)1 << 18) {
     e = launch_gemm_f32(b, wr, logits, T, E, d, st);
   } else {
     hipLaunchKernelGGL(k_moe_logits, dim3((T + kMoeTokens - 1) / kMoeTokens, E / 16), dim3(64), 0, st, b, wr, T, d, E,

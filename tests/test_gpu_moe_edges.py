@@ -1,7 +1,8 @@
 """The mixture-of-experts block where its kernels change: the sorted order by
 one block and by several (from 4096 assignments), logits by wavefronts and by
-the weight-streaming GEMM (above 2048 tokens), expert products in 64-row
-tiles and in 256-row ones, hidden sizes and widths that end inside a stage.
+the weight-streaming GEMM (above 2^18 token-expert pairs), expert products in
+64-row tiles and in 256-row ones, hidden sizes and widths that end inside a
+stage.
 
 Reference in float64 under the routing the block reports, which must be a
 valid top k.  The bound per element: the result and each m are rounded to bf16
@@ -23,6 +24,7 @@ pytestmark = pytest.mark.gpu
     (128, 32, 3, 64, 1500),      # many rows per expert, too little work for 256-row tiles
     (512, 16, 4, 576, 1000), (512, 16, 4, 512, 1023), (512, 16, 4, 512, 1024),   # 256-row tiles; both sides of 2^30
     (4096, 16, 8, 64, 520),      # 256-row tiles of a single K tile down
+    (160, 256, 2, 24, 1024), (160, 256, 2, 24, 1025), (96, 16, 1, 8, 16384), (96, 16, 1, 8, 16385),   # logits, both sides
     (2080, 48, 5, 24, 70), (64, 16, 16, 8, 300)])
 def test_moe_edges(d, E, k, F, T):
     shape = gen.MoeShape("edge", d, E, k, F)
