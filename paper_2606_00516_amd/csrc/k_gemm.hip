@@ -443,10 +443,10 @@ struct GroupedArgs {
 // ssq[split][M]; the row scale 1 / sqrt(mean(x^2) + eps) is applied to the
 // summed partials by the consumer (RMSNorm(x) g W^T = inv * ((x g) W^T)).
 //
-// GROUPED: the experts of a mixture-of-experts block with a few rows each.
-// Half the LDS per block, so that a block's start is hidden by its neighbour
-// (a block lasts 32 stages or less), an expert's column tiles side by side on
-// one XCD.  128 experts of 768 over hidden 2048, 64 tokens: gate/up 151 -> 134
+// GROUPED (its waves a block): the experts of a mixture-of-experts block with a
+// few rows each.  Half the LDS per block, so that a block's start is hidden by
+// its neighbour (a block lasts 32 stages or less), an expert's column tiles
+// side by side on one XCD.  128 experts of 768 over hidden 2048, 64 tokens: gate/up 151 -> 134
 // us (6.0 TB/s), down 85 -> 73 against the register-staged 64 x 64 tiles it
 // replaced; 512 tokens 172 + 100 -> 147 + 84.
 // ===========================================================================
@@ -455,7 +455,7 @@ constexpr int ST_BN = 128;  // logical columns per block
 // A rows of KC values (bf16: 64, rows of 128 bytes; 8-bit W: 128, W rows of
 // 128 bytes of codes), the ring fills the CU's LDS (160 KiB less the norm
 // gains), all but one stage of it in flight.
-template <int BM, bool W8, bool PRENORM, bool GROUPED = false>
+template <int BM, bool W8, bool PRENORM, int GROUPED = 0>
 struct StreamTraits {
   static constexpr int KC = W8 ? 128 : 64;
   static constexpr int WROW = KC * (W8 ? 1 : 2);       // bytes of a W row
@@ -467,15 +467,15 @@ struct StreamTraits {
   static constexpr int R = (GROUPED ? 80 * 1024 : 160 * 1024) / STAGE;  // (grouped: two blocks per CU)
   static constexpr int LDS = R * STAGE;
   static_assert(R >= 2, "ring depth");
-  static constexpr int NW = GROUPED ? 4 : 8;          // waves: two on each SIMD (grouped: one of each of two blocks)
-  static constexpr int WM = GROUPED ? 1 : BM >= 128 ? 4 : 2, WN = NW / WM;  // wave grid
+  static constexpr int NW = GROUPED ? GROUPED : 8;  // waves: two on each SIMD (grouped, 4: one of each of two blocks)
+  static constexpr int WM = NW == 4 ? 1 : BM >= 128 ? 4 : 2, WN = NW / WM;  // wave grid
   static constexpr int NF = ST_BN / WN / 16;          // 16-column fragments per wave
   static constexpr int NI = BM / WM / 16;             // 16-row blocks per wave
   static constexpr int LA = A_BYTES / (NW * 1024), LW = W_BYTES / (NW * 1024);  // load instructions per wave and stage
   static_assert(LA * NW * 1024 == A_BYTES && LW * NW * 1024 == W_BYTES && NI * WM * 16 == BM, "wave shares");
 };
 
-template <int BM, bool W8, bool PRENORM, bool GROUPED = false, bool ONCE = false>
+template <int BM, bool W8, bool PRENORM, int GROUPED = 0, bool ONCE = false>
 __global__ __launch_bounds__((64 * StreamTraits<BM, W8, PRENORM, GROUPED>::NW)) void k_gemm_stream(
     const uint16_t *__restrict__ A, const void *__restrict__ W, const float *__restrict__ wscale,
     uint16_t *__restrict__ out, const uint16_t *__restrict__ res, float *__restrict__ part, int M, int N, int K, int epi,
@@ -1492,7 +1492,7 @@ static hipError_t launch_stream(const uint16_t *A, const void *W, const float *w
   const dim3 grid(8 * per_xcd, splits);
   const bool once = w_read_once(mt, M, N, K, w8);
 #define EB_STREAM(BM_, W8_)                                                                                         \
-  hipLaunchKernelGGL((once ? k_gemm_stream<BM_, W8_, PRENORM, false, true> : k_gemm_stream<BM_, W8_, PRENORM>), grid, \
+  hipLaunchKernelGGL((once ? k_gemm_stream<BM_, W8_, PRENORM, 0, true> : k_gemm_stream<BM_, W8_, PRENORM>), grid, \
                      dim3(64 * StreamTraits<BM_, W8_, PRENORM>::NW), (StreamTraits<BM_, W8_, PRENORM>::LDS), st, A, W, \
                      wscale, out, res, part, M, N, K, epi, per, tiles, mt, per_xcd, gamma, ssq, GroupedArgs{})
   if (bm == 64) {
@@ -1625,9 +1625,16 @@ hipError_t launch_gemm_grouped(const uint16_t *A, int a_nrows, const int32_t *a_
   const GroupedArgs ga{a_rows, tiles, n_tiles, max_tiles, a_nrows, f32_out ? 1 : 0};
   uint16_t *o16 = f32_out ? nullptr : static_cast<uint16_t *>(out);
   float *o32 = f32_out ? static_cast<float *>(out) : nullptr;
-  hipLaunchKernelGGL((once ? k_gemm_stream<64, false, false, true, true> : k_gemm_stream<64, false, false, true>),
-                     dim3(grid), dim3(256), (StreamTraits<64, false, false, true>::LDS), st, A, W, nullptr, o16, nullptr,
-                     o32, 0, N, K, epi, (K + 31) / 32, 0, nct, 0, nullptr, nullptr, ga);
+  // Eight waves a block where all blocks are on the chip at once, two per CU, and
+  // each one's own latency counts (16 experts of 512 over 1024: one token 24.8 ->
+  // 23.4 us, 16 tokens 29.3 -> 28.5; 32 experts the same 26.4 -> 25.0, 33.2 -> 32.3);
+  // with more, four (16 experts of 2048 over 4096, 64 tokens: 176 against 178).
+  const bool wide = grid <= 512;
+  auto k = wide ? (once ? k_gemm_stream<64, false, false, 8, true> : k_gemm_stream<64, false, false, 8>)
+                : (once ? k_gemm_stream<64, false, false, 4, true> : k_gemm_stream<64, false, false, 4>);
+  static_assert(StreamTraits<64, false, false, 8>::LDS == StreamTraits<64, false, false, 4>::LDS, "one LDS size");
+  hipLaunchKernelGGL(k, dim3(grid), dim3(wide ? 512 : 256), (StreamTraits<64, false, false, 4>::LDS), st, A, W, nullptr,
+                     o16, nullptr, o32, 0, N, K, epi, (K + 31) / 32, 0, nct, 0, nullptr, nullptr, ga);
   return hipGetLastError();
 }
 
