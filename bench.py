@@ -67,7 +67,7 @@ def parse():
                     help="projection weights: bf16, or 8-bit E4M3 codes with one fp32 scale per output row")
     ap.add_argument("--packed-weights", default="on", choices=["on", "off"],
                     help="single-layer workloads: give the step fragment-packed copies of the bf16 projections "
-                         "(made once, before timing; read by the weight-streaming GEMMs of steps under 256 rows)")
+                         "(made once, before timing; read by the steps of at most 64 rows)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extras", action="store_true",
                     help="decode8b: skip the prefill step and the MB sweep that the default line carries")

@@ -136,11 +136,10 @@ typedef struct eb_layer_weights {
    * unused otherwise) */
   const void *q_norm, *k_norm;
   /* optional fragment-packed copies of the four bf16 projections
-   * (eb_pack_weight; NULL: none).  The weight-streaming GEMMs (steps of at
-   * most 256 rows) read a packed copy instead of the row-major matrix, the
-   * same values in the same order, so outputs are bitwise unchanged; the
-   * 256 x 256 tiled GEMMs always read the row-major matrices, which stay
-   * required.  Ignored for 8-bit weights and for a matrix whose shape
+   * (eb_pack_weight; NULL: none).  Steps of at most 64 rows read a packed
+   * copy instead of the row-major matrix, the same values in the same order,
+   * so outputs are bitwise unchanged; larger steps always read the row-major
+   * matrices, which stay required.  Ignored for 8-bit weights and for a matrix whose shape
    * eb_packed_weight_bytes rejects.  A packed copy must be made from the
    * matrix it stands beside; the library cannot check that. */
   const void *p_qkv, *p_o, *p_gate_up, *p_down;

@@ -2,13 +2,15 @@
 // W [N, K] weights, both K-contiguous bf16, fp32 accumulation on the
 // 16x16x32 bf16 MFMA.
 //
-//  * stream: decode-sized batches (up to 256 rows, all of them in one block
-//    of 128 columns, one block per CU).  The product is bound by streaming W
-//    from HBM once: W and A go straight into an LDS ring that fills the CU,
-//    all but one stage of it in flight, and blocks may further split K, with
-//    a small reduction kernel applying the epilogue.  Up to 64 rows, W may
-//    come from a fragment-packed copy straight into registers.
-//  * big: 256 x 256 tiles, larger M.
+//  * stream: decode-sized batches (below 256 rows, and any number of them
+//    against a W that one XCD's L2 holds) in blocks of 64 to 256 rows x 128
+//    columns, one block per CU.  The product is bound by streaming W from HBM
+//    once: W and A go straight into an LDS ring that fills the CU, all but one
+//    stage of it in flight, and blocks may further split K, with a small
+//    reduction kernel applying the epilogue.  Up to 64 rows, W may come from a
+//    fragment-packed copy straight into registers.
+//  * big: 256 x 256 tiles, larger M (and from 129 rows where its estimated
+//    time is the least: plan_gemm).
 //  * tiled: what neither takes.  128x128 output tiles, K tiles of 64
 //    double-buffered in LDS, 4 waves each owning a 64x64 sub-tile.
 //
@@ -151,7 +153,11 @@ __global__ __launch_bounds__(256) void k_pack_weight(const uint16_t *__restrict_
 // through LDS (three buffers).  The products take the same operands in the
 // same order, so the sums are bitwise those of k_gemm_stream<64, false>.
 // It stays for up to 64 rows because its split products are faster (8B down
-// 24.7 against 29.7 us, qkv with the norm 15.6 against 18.2, o the same).
+// 24.7 against 29.7 us, qkv with the norm 15.6 against 18.2, o the same).  With
+// more rows its 64-row blocks pass over W once each and the wider blocks of
+// k_gemm_stream are faster on the row-major matrix (8B step at short contexts,
+// 66 rows 195 us packed, 143 row-major; 128 rows 205, 177; 255 rows 306, 256;
+// 70B layer, 80 rows 570, 382; 192 rows 734, 502).
 constexpr int SP_LDS = 3 * SK_BM * SK_ROWB;
 constexpr int SP_LDS_ONE = 96 * 1024;  // as launched: keeps one block per CU
 static_assert(SP_LDS_ONE >= SP_LDS, "LDS");
