@@ -1479,6 +1479,10 @@ static void launch_big(dim3 grid, hipStream_t st, const uint16_t *A, const void 
 // 40.0, of 8-bit codes 29.7 -> 28.0.  To 32 rows for every W larger than one
 // XCD's L2; above, where activations and partials weigh more, from 96 MiB (8B
 // qkv, 50 MB, at 64 rows 15.6 -> 17.4 with them, 8B down, 117 MB, 31.0 -> 28.8).
+// Between the two sizes it depends on what the caches hold: passes over one 8B
+// layer, 64 requests, 213 -> 218 us with them; twelve layers in turn 1684 -> 1707,
+// with 8-bit W at 37 rows 1294 -> 1271; after a flush that left the caches
+// full of written data 251 -> 239.
 static bool w_read_once(int mt, int M, int N, int K, bool w8) {
   const size_t bytes = (size_t)N * K * (w8 ? 1 : 2);
   return mt == 1 && bytes > (M <= 32 ? (size_t)4 << 20 : (size_t)96 << 20);
