@@ -134,6 +134,10 @@ MoeBufs moe_bufs(const MoeArgs &a) {
   // block has so little work that the start and end of a large tile are most
   // of it (blocks of 16 experts of 128 over 256: 128 rows each 25 us streamed,
   // 37 in 256 x 256 tiles; 1024 rows each 48 against 55, 2048 62 against 60)
+  // (the line over 11 shapes of 16 to 256 experts and 32 to 400 rows each: within
+  // 10 % of the better side where the large tiles are a block per CU or more; with
+  // fewer the 64-row tiles stay ahead longer, 16 experts of 1024 over 2048, 128
+  // blocks, 100 rows each 62 us against 86, 200 rows 99 against 93)
   // (a 256-row tile's outputs, fp32 [d] and bf16 [F], stay inside a 32-bit buffer range)
   const bool fits = (size_t)256 * a.d * 4 < ((size_t)1 << 31) && (size_t)256 * a.F * 2 < ((size_t)1 << 31);
   const bool work = (size_t)a.T * a.k * a.d * a.F >= (size_t)1 << 30;
